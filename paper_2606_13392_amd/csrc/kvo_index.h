@@ -100,7 +100,8 @@ constexpr int kHistBins = 16384;
 __global__ __launch_bounds__(256) void kvo_count_kernel(const int32_t* __restrict__ block_ids, msa_seqs sq,
                                                         const int64_t* __restrict__ blk_base, int H_kv, int BK,
                                                         int topk, int64_t nbcap, int64_t row0, int64_t nrows,
-                                                        int32_t* __restrict__ cnt, int32_t* __restrict__ tpos) {
+                                                        int p_min, int32_t* __restrict__ cnt,
+                                                        int32_t* __restrict__ tpos) {
   __shared__ int32_t hist[kHistBins];
   const int r = blockIdx.y;
   const int64_t rb0 = row0 + static_cast<int64_t>(blockIdx.x) * kHistRows;
@@ -124,6 +125,7 @@ __global__ __launch_bounds__(256) void kvo_count_kernel(const int32_t* __restric
   for (int64_t row = rb0 + threadIdx.x; row < rb1; row += 256) {
     int s;
     const int p = row_position(sq, row, &s);
+    if (p < p_min) continue;
     const int32_t* ids = block_ids + (row * H_kv + r) * topk;
     int32_t* tp = tpos + ((row - row0) * H_kv + r) * topk;
     const int64_t gb0 = blk_base[s];
@@ -159,6 +161,7 @@ __global__ __launch_bounds__(256) void kvo_count_kernel(const int32_t* __restric
   for (int64_t row = rb0 + threadIdx.x; row < rb1; row += 256) {
     int s;
     const int p = row_position(sq, row, &s);
+    if (p < p_min) continue;
     const int32_t* ids = block_ids + (row * H_kv + r) * topk;
     int32_t* tp = tpos + ((row - row0) * H_kv + r) * topk;
     const int64_t gb0 = blk_base[s];
@@ -187,7 +190,7 @@ __global__ __launch_bounds__(256) void kvo_count_kernel(const int32_t* __restric
 __global__ __launch_bounds__(256) void kvo_fill_kernel(const int32_t* __restrict__ block_ids, msa_seqs sq,
                                                        const int64_t* __restrict__ blk_base, int H_kv, int BK,
                                                        int topk, int64_t nbcap, int64_t row0, int64_t nrows,
-                                                       const int32_t* __restrict__ tile_off,
+                                                       int p_min, const int32_t* __restrict__ tile_off,
                                                        const int32_t* __restrict__ tpos,
                                                        uint32_t* __restrict__ handles) {
   const int lane = lane_id();
@@ -198,6 +201,7 @@ __global__ __launch_bounds__(256) void kvo_fill_kernel(const int32_t* __restrict
   const int r = static_cast<int>(i % H_kv);
   int s;
   const int p = row_position(sq, row, &s);
+  if (p < p_min) return;
   const int32_t* ids = block_ids + (row * H_kv + r) * topk;
   const int32_t* tp = tpos + i * topk;
   const int64_t base = static_cast<int64_t>(r) * nbcap + blk_base[s];
@@ -521,18 +525,19 @@ __global__ __launch_bounds__(256) void rank_tile_handles_kernel(uint32_t* __rest
 }
 
 // Reverse index of query rows r0 .. r0 + nr - 1 (one chunk): counts, scans
-// and handle lists for every tile of H_kv x nbcap; `canonical` sorts each list.
+// and handle lists for every tile of H_kv x nbcap; `canonical` sorts each
+// list.  Rows at positions below p_min stay out of it.
 void build_reverse_index(const int32_t* block_ids, const msa_seqs& sq, const int64_t* blk_base, int H_kv, int BK,
                          int topk, int64_t nbcap, int64_t ntile, int nscan, int64_t r0, int64_t nr, int32_t* cnt,
                          int32_t* tile_off, int32_t* item_off, int32_t* blk_tot, int32_t* tpos, uint32_t* handles,
-                         hipStream_t stream, bool canonical = false) {
+                         hipStream_t stream, bool canonical = false, int p_min = INT32_MIN) {
   const unsigned fill_blocks = static_cast<unsigned>(std::min<int64_t>((ntile + kWorkCounters + 255) / 256, 4096));
   const unsigned gthreads = static_cast<unsigned>((nr * H_kv + 256 / kWave - 1) / (256 / kWave));   // a wave per pair
   msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, cnt,
                    ntile + kWorkCounters, 0);
   const dim3 hgrid(static_cast<unsigned>((nr + kHistRows - 1) / kHistRows), static_cast<unsigned>(H_kv));
   msa_prof::launch("kvo_count_kernel", kvo_count_kernel, hgrid, dim3(256), 0, stream, block_ids, sq, blk_base, H_kv,
-                   BK, topk, nbcap, r0, nr, cnt, tpos);
+                   BK, topk, nbcap, r0, nr, p_min, cnt, tpos);
   msa_prof::launch("kvo_scan_block_kernel", kvo_scan_block_kernel, dim3(nscan), dim3(256), 0, stream, cnt, ntile,
                    tile_off, item_off, blk_tot);
   msa_prof::launch("kvo_scan_top_kernel", kvo_scan_top_kernel, dim3(1), dim3(1024), 0, stream, blk_tot, nscan,
@@ -540,7 +545,7 @@ void build_reverse_index(const int32_t* block_ids, const msa_seqs& sq, const int
   msa_prof::launch("kvo_scan_add_kernel", kvo_scan_add_kernel, dim3(static_cast<unsigned>((ntile + 255) / 256)),
                    dim3(256), 0, stream, blk_tot, ntile, tile_off, item_off);
   msa_prof::launch("kvo_fill_kernel", kvo_fill_kernel, dim3(gthreads), dim3(256), 0, stream, block_ids, sq, blk_base,
-                   H_kv, BK, topk, nbcap, r0, nr, tile_off, tpos, handles);
+                   H_kv, BK, topk, nbcap, r0, nr, p_min, tile_off, tpos, handles);
   // positions are no longer needed: tpos is the long tiles' scatter buffer
   if (canonical) {
     msa_prof::launch("sort_tile_handles_kernel", sort_tile_handles_kernel, dim3(static_cast<unsigned>(ntile)),

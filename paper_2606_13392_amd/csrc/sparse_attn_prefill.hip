@@ -24,6 +24,12 @@
 
 #include "kvo_index.h"
 
+// rows of short causal contexts (sparse_attn_tile.hip)
+int msa_tile_positions(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk);
+int msa_tile_prefill(const void* q, const void* k, const void* v, const int32_t* block_ids, const msa_seqs* seqs,
+                     int H_q, int H_kv, int BK, int topk, int p_cut, float scale_log2, float o_scale, void* o,
+                     float* lse, hipStream_t stream, bool fp8);
+
 namespace {
 
 using namespace msa;
@@ -323,13 +329,13 @@ constexpr int kCombineWaves = 4;
 template <int PER>
 __global__ __launch_bounds__(64 * kCombineWaves) void kvo_combine_kernel(
     const int32_t* __restrict__ block_ids, msa_seqs sq, const int64_t* __restrict__ blk_base, int H_q, int H_kv,
-    int BK, int topk, int64_t row0, int64_t nrows, const uint16_t* __restrict__ o_buf,
+    int BK, int topk, int64_t row0, int64_t nrows, int p_min, const uint16_t* __restrict__ o_buf,
     const float* __restrict__ lse_buf, uint16_t* __restrict__ o, float* __restrict__ lse) {
   __shared__ float s_w[kCombineWaves][64][17];        // weight of slot j for head hh (G <= 16)
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
   int64_t pr = static_cast<int64_t>(blockIdx.x) * kCombineWaves + wave;   // (row, group) pair
-  const bool active = pr < nrows * H_kv;
+  bool active = pr < nrows * H_kv;
   if (!active) pr = 0;                               // computes a row it does not store
   const int64_t rl = pr / H_kv;
   const int r = static_cast<int>(pr % H_kv);
@@ -337,8 +343,9 @@ __global__ __launch_bounds__(64 * kCombineWaves) void kvo_combine_kernel(
   const int64_t row = row0 + rl;
   int s;
   const int p = row_position(sq, row, &s);
+  if (p < p_min) active = false;                     // the tile kernel's row
   const int32_t* ids = block_ids + (row * H_kv + r) * topk;
-  const bool valid = lane < topk && incidence_ok(ids[lane], p, BK, blk_base, s);
+  const bool valid = active && lane < topk && incidence_ok(ids[lane], p, BK, blk_base, s);
   const float* lrow = lse_buf + (rl * H_kv + r) * static_cast<int64_t>(topk) * G;
   // per head: max and sum over the valid slots (lane j = slot j)
   float tot[16];
@@ -563,11 +570,18 @@ int msa_kvo_prefill(const void* q, const void* k, const void* v, const int32_t* 
   auto* op = static_cast<uint16_t*>(o);
   const float sl2 = scale * q_scale * k_scale * kLog2e;
 
+  // rows at positions below p_cut go to the tile kernel, the others key-block-outer
+  const int p_cut = msa_tile_positions(seqs, H_q, H_kv, BK, topk);
+  if (p_cut > 0) {
+    st = msa_tile_prefill(q, k, v, block_ids, seqs, H_q, H_kv, BK, topk, p_cut, sl2, v_scale, o, lse, stream, fp8);
+    if (st != MSA_OK || seqs->max_kv_len <= p_cut) return st != MSA_OK ? st : msa_host::launch_status();
+  }
+  const int p_min = p_cut > 0 ? p_cut : INT32_MIN;
   msa_prof::launch("kvo_block_base_kernel", kvo_block_base_kernel, dim3(1), dim3(256), 0, stream, sq, BK, blk_base);
   for (int64_t r0 = 0; r0 < seqs->total_q_rows; r0 += pl.chunk_rows) {
     const int64_t nr = std::min<int64_t>(pl.chunk_rows, seqs->total_q_rows - r0);
     build_reverse_index(block_ids, sq, blk_base, H_kv, BK, topk, pl.nbcap, pl.ntile, pl.nscan, r0, nr, cnt, tile_off,
-                        item_off, blk_tot, tpos, handles, stream);
+                        item_off, blk_tot, tpos, handles, stream, false, p_min);
     if (BK == 64 && !fp8)
       launch_kvo_attn<64, uint16_t>(q, k, v, sq, blk_base, tile_off, item_off, handles, H_q, H_kv, topk, pl.nbcap, r0,
                                     sl2, v_scale, o_buf, lse_buf, cnt + pl.ntile, stream);
@@ -585,7 +599,7 @@ int msa_kvo_prefill(const void* q, const void* k, const void* v, const int32_t* 
     auto combine = G <= 4 ? kvo_combine_kernel<8> : (G <= 8 ? kvo_combine_kernel<16> : kvo_combine_kernel<32>);
     msa_prof::launch("kvo_combine_kernel", combine, dim3(static_cast<unsigned>((pairs + kCombineWaves - 1) / kCombineWaves)),
                      dim3(64 * kCombineWaves), 0, stream, block_ids, sq, blk_base, H_q, H_kv, BK, topk, r0, nr,
-                     o_buf, lse_buf, op, lse);
+                     p_min, o_buf, lse_buf, op, lse);
   }
   return msa_host::launch_status();
 }

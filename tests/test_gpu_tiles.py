@@ -1,0 +1,118 @@
+"""Prefill Main Branch by query tiles (rows of short causal contexts).
+
+Prefill calls whose rows select much of their causal context run the tile
+kernel.  Cases sit where it can go wrong: row counts around a tile, contexts
+around key sub-blocks and blocks, group sizes that do not divide a wave's 32
+rows, ids in any order with padding, out-of-range entries and empty rows,
+E4M3, pages, and calls split between tiles and key-block-outer kernels.
+Sampled rows are compared with the float64 oracle, all rows with the decode
+call (another kernel for the same attention): both round weights and outputs
+to bf16, so they differ by at most two roundings of 2^-9 each way, 5e-3.
+"""
+from __future__ import annotations
+
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+import oracle.msa_oracle as O
+from paper_2606_13392_amd import msa, synth
+from tests.util import check_outputs, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    msa.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+# name, q_rows, kv_lens, H_q, H_kv, block, topk, fp8, paged, tiles only
+CASES = [
+    ("tile_edges", [255, 256, 257, 1, 15, 16, 17], [255, 256, 257, 1, 15, 16, 17], 64, 8, 64, 4, False, False, True),
+    ("bk128_g16_pages", [127, 129, 385, 8, 9], [127, 129, 385, 8, 9], 64, 4, 128, 3, False, True, True),
+    ("fp8_pages", [300, 64, 65], [300, 64, 65], 64, 8, 64, 5, True, True, True),
+    ("fp8_bk128", [500, 63], [500, 63], 64, 4, 128, 4, True, False, True),
+    ("g3_context", [200, 131, 70], [650, 131, 710], 48, 16, 64, 12, False, False, True),
+    ("g5_fp8", [190, 77], [190, 77], 80, 16, 64, 6, True, False, True),
+    ("g1", [260, 600], [260, 900], 32, 32, 64, 16, False, True, True),
+    ("k1_local_only", [256, 130], [256, 130], 64, 8, 64, 1, False, False, True),
+    ("k64_many_groups", [400], [400], 64, 32, 64, 63, False, False, True),
+    ("split_at_reach", [3600], [3600], 64, 8, 64, 3, False, False, False),
+    ("split_bk128_pages_fp8", [3600, 700], [3600, 700], 64, 8, 128, 2, True, True, False),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_tiles(case):
+    name, q_rows, kv_lens, H_q, H_kv, bk, topk, fp8, paged, only = case
+    p = synth.packed_problem(name, q_rows, kv_lens, num_q_heads=H_q, num_kv_heads=H_kv, block_size=bk, topk=topk,
+                             seed=zlib.crc32(name.encode()) % 10000)
+    x = (synth.generate_fp8_numpy if fp8 else synth.generate_numpy)(p)
+    rng = np.random.default_rng(p.seed)
+    ids = synth.random_block_ids(p, pad_slots=1)
+    # slots in any order; one entry past the local block, where a slot is free; every 50th (row, group) empty
+    ids = rng.permuted(ids, axis=2)
+    pos = p.positions()
+    for row in range(p.total_q_rows):
+        free = np.argwhere(ids[row] < 0)
+        for g, j in free[:1]:
+            ids[row, g, j] = pos[row] // bk + 1
+    ids.reshape(-1, topk + 1)[::50] = -1
+    dev = torch.device("cuda")
+    up = (lambda a: torch.from_numpy(a).to(dev)) if fp8 else to_dev
+    q, k, v, seqs = up(x["q"]), up(x["k"]), up(x["v"]), msa.Seqs.from_problem(p, dev)
+    if paged:
+        nb = [-(-n // bk) for n in kv_lens]
+        pages = rng.permutation(sum(nb) + 3)
+        table = np.zeros((len(nb), max(nb)), dtype=np.int32)
+        pool = torch.zeros(((sum(nb) + 3) * bk, H_kv, 128), dtype=k.dtype, device=dev)
+        pk, pv, at = pool, pool.clone(), 0
+        for s, n in enumerate(nb):
+            for b in range(n):
+                table[s, b] = pages[at]
+                at += 1
+                rows = min(bk, kv_lens[s] - b * bk)
+                src, dst = p.kv_starts[s] + b * bk, int(table[s, b]) * bk
+                pk[dst:dst + rows] = k[src:src + rows]
+                pv[dst:dst + rows] = v[src:src + rows]
+        k, v = pk, pv
+        seqs = msa.Seqs(q_rows, kv_lens, [0] * len(nb), pool.shape[0], dev, block_table=torch.from_numpy(table).to(dev),
+                        page_size=bk)
+    ids_d = torch.from_numpy(ids).to(dev)
+    scales = synth.FP8_SCALES
+
+    def call(kind):
+        fn = getattr(msa, f"sparse_attn_{kind}" + ("_fp8" if fp8 else ""))
+        return fn(q, k, v, scales, ids_d, seqs, bk) if fp8 else fn(q, k, v, ids_d, seqs, bk)
+
+    msa.profile_reset()
+    msa.profile_enable(True)
+    try:
+        o, lse = call("prefill")
+        torch.cuda.synchronize()
+    finally:
+        msa.profile_enable(False)
+    launched = msa.profile_read()
+    msa.profile_reset()
+    assert "tile_attn_kernel" in launched and ("kvo_attn_kernel" not in launched) == only
+    od, ld = call("decode")
+    torch.cuda.synchronize()
+    seen = torch.isfinite(ld)
+    assert torch.equal(seen, torch.isfinite(lse)) and not bool(seen.all())
+    assert bool((o[~seen] == 0).all()) and bool((lse[~seen] == ld[~seen]).all())
+    assert float((lse - ld)[seen].abs().max()) <= 1e-4
+    diff = (o.double() - od.double()).norm() / od.double().norm()
+    assert float(diff) <= 5e-3
+    # the oracle on sampled rows that attend something in every group
+    full = [r for r in range(p.total_q_rows) if bool(seen[r].all())]
+    rows = sorted(set(rng.choice(full, size=24).tolist() + full[:2] + full[-2:]))
+    o_ref, l_ref = O.sparse_attention(x["q"], x["k"], x["v"], ids, O.layout_of(p), bk, rows=rows,
+                                      fmt="e4m3" if fp8 else "bf16", input_scales=scales if fp8 else (1.0, 1.0, 1.0))
+    check_outputs(o[rows].float().cpu().numpy(), lse[rows].cpu().numpy(), o_ref, l_ref, name)
