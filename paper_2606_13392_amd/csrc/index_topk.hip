@@ -12,19 +12,20 @@
 // Work units: a row group is qr = 64 / H_kv consecutive query rows of one
 // sequence (64 index rows: query row x group, contiguous in index_q); a unit is
 // U consecutive row groups of one sequence.  Per chunk of units:
-//   index_block_max_lds   (U = 4, prefill) one CTA = 4 waves = 256 index rows
-//                         sharing each K_idx block through a double-buffered LDS
-//                         ring fed by register prefetch two blocks ahead;
+//   index_block_max_lds   (U >= 4, prefill) one CTA = 4 waves = 256 or 512 index
+//                         rows sharing each K_idx block through a double-buffered
+//                         LDS ring filled by DMA one sub-block ahead;
 //   index_block_max_wave  (U = 1, few rows per sequence, e.g. decode) one wave
 //                         per row group and slice of key blocks;
 // both run MFMA 32x32x16 with keys as M and index rows as N, reduce the block
 // max in registers plus one permlane32 swap and write M[row][block] (fp32);
-//   index_topk            one wave per index row streams M[row][0..lb) 64
-//                         blocks at a time, filters against the current k-1-th
-//                         best key and keeps a sorted list (one key per lane).
+//   index_topk            one wave per index row: a bound that at least k-1 of
+//                         the row's scores reach, then a radix search among the
+//                         few dozen scores above it.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "msa_common.h"
 #include "msa_profile.h"
@@ -37,34 +38,11 @@ constexpr int kWaves = 4;
 constexpr int kBlocksPerCta = 64;      // key blocks per CTA slice, LDS kernel
 constexpr int kSmallInsert = 6;        // survivors per 64-block step inserted one by one
 
-// ---------------------------------------------------------------- setup
-// unit_off[s] = units before sequence s.
-__global__ __launch_bounds__(256) void unit_offsets_kernel(msa_seqs sq, int qr, int U,
-                                                           int32_t* __restrict__ unit_off) {
-  __shared__ int32_t part[256];
-  const int t = threadIdx.x;
-  const int S = sq.num_seqs;
-  const int per = (S + 255) / 256;
-  const int s0 = t * per, s1 = min(S, s0 + per);
-  auto units = [&](int s) -> int32_t {
-    const int rows = sq.q_offsets[s + 1] - sq.q_offsets[s];
-    const int groups = rows > 0 ? (rows + qr - 1) / qr : 0;
-    return (groups + U - 1) / U;
-  };
-  int32_t acc = 0;
-  for (int s = s0; s < s1; ++s) acc += units(s);
-  part[t] = acc;
-  __syncthreads();
-  if (t == 0) {
-    int32_t run = 0;
-    for (int i = 0; i < 256; ++i) { int32_t x = part[i]; part[i] = run; run += x; }
-    unit_off[S] = run;
-  }
-  __syncthreads();
-  acc = part[t];
-  for (int s = s0; s < s1; ++s) { unit_off[s] = acc; acc += units(s); }
-}
-
+// ---------------------------------------------------------------- units
+// A unit holds 2^unit_shift query rows of one sequence; sequence s owns units
+// from q_offsets[s] / 2^unit_shift + s on, at least as many as it needs.  With
+// unit_shift < 0 (every sequence has at most one row group and U = 1) unit s
+// is sequence s.
 struct UnitRows {
   bool ok;
   int s;
@@ -73,23 +51,32 @@ struct UnitRows {
   int nq;       // valid query rows in the unit
 };
 
-// Without a unit table (every sequence has at most one row group and U = 1)
-// unit s is sequence s.
-__device__ __forceinline__ UnitRows locate_unit(const msa_seqs& sq, const int32_t* __restrict__ unit_off,
-                                                int64_t uidx, int qr, int U) {
+__device__ __forceinline__ UnitRows locate_unit(const msa_seqs& sq, int unit_shift, int64_t uidx, int qr, int U) {
   UnitRows r;
   r.ok = false;
-  if (!unit_off) {
+  if (unit_shift < 0) {
     if (uidx >= sq.num_seqs) return r;
     r.s = static_cast<int>(uidx);
-    r.g = seq_geom(sq, r.s);
     r.t0 = 0;
   } else {
-    if (uidx >= unit_off[sq.num_seqs]) return r;
-    r.s = find_seq_wave(unit_off, sq.num_seqs, uidx);
-    r.g = seq_geom(sq, r.s);
-    r.t0 = static_cast<int>(uidx - unit_off[r.s]) * qr * U;
+    int lo = 0, n = sq.num_seqs;               // the sequence lies in [lo, lo + n)
+    while (n > 1) {
+      const int stride = (n + kWave - 1) / kWave;
+      const int idx = lo + lane_id() * stride;
+      const bool ok = idx < lo + n && static_cast<int64_t>(sq.q_offsets[idx] >> unit_shift) + idx <= uidx;
+      const uint64_t mask = __ballot(ok);      // a prefix of the lanes: the first units increase
+      const int j = 63 - __clzll(static_cast<long long>(mask | 1ull));
+      const int lo_new = lo + j * stride;
+      n = min(stride, lo + n - lo_new);
+      lo = lo_new;
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    r.s = lo;
+    const int64_t t0 = (uidx - (sq.q_offsets[lo] >> unit_shift) - lo) << unit_shift;
+    if (t0 < 0 || t0 >= sq.total_q_rows) return r;
+    r.t0 = __builtin_amdgcn_readfirstlane(static_cast<int>(t0));
   }
+  r.g = seq_geom(sq, r.s);
   r.nq = min(qr * U, r.g.q_rows - r.t0);
   // never touch query rows past the query-side tensors
   const int64_t left = sq.total_q_rows - (static_cast<int64_t>(r.g.q_begin) + r.t0);
@@ -137,7 +124,7 @@ __device__ __forceinline__ float block_max_rows(const f32x16 (&acc)[MT][NJ], int
 constexpr int kStageBlocks = 16;      // block maxima staged per row before a 64-byte store
 constexpr int kPieceBlocks = 16;      // blocks per piece maximum (the Top-k's finer skip test)
 constexpr int kSurvivorCap = 1024;    // pieces per round of the Top-k's piece scan
-constexpr int kSlicePieces = 4;       // pieces per 64-block CTA slice: PM[slice][row][4]
+constexpr int kSlicePieces = 4;       // pieces per 64-block slice: PM[slice][row][4]
 
 // One 16-byte piece per lane from global memory straight into LDS
 // (global_load_lds_dwordx4): lane l writes bytes [16 l, 16 l + 16) after the
@@ -170,7 +157,7 @@ struct IdxSmem {
 template <int D_IDX, int BK, int RW, bool PAGED>
 __global__ __launch_bounds__(256, (RW == 64) ? 3 : 2) void index_block_max_lds_kernel(
     const uint16_t* __restrict__ index_q, const uint16_t* __restrict__ index_k, msa_seqs sq,
-    const int32_t* __restrict__ unit_off, int H_kv, int qr, int64_t u0, int64_t u1, float* __restrict__ M,
+    int unit_shift, int H_kv, int qr, int64_t u0, int64_t u1, int cta_blocks, float* __restrict__ M,
     int64_t ldm, float* __restrict__ CM, int64_t cm_stride, float* __restrict__ PM) {
   static_assert(kBlocksPerCta == kWave, "a CTA slice is one Top-k chunk");
   static_assert(kStageBlocks == kPieceBlocks, "a piece ends where a store pass does");
@@ -185,12 +172,13 @@ __global__ __launch_bounds__(256, (RW == 64) ? 3 : 2) void index_block_max_lds_k
   const int w = threadIdx.x / kWave;
   const int64_t uidx = u0 + blockIdx.x;
   if (uidx >= u1) return;
-  UnitRows ur = locate_unit(sq, unit_off, uidx, qr, kWaves * NP);
+  UnitRows ur = locate_unit(sq, unit_shift, uidx, qr, kWaves * NP);
   if (!ur.ok) return;
   const int p_last = ur.g.kv_len - ur.g.q_rows + ur.t0 + ur.nq - 1;
   if (p_last < 0) return;
-  const int kb0 = blockIdx.y * kBlocksPerCta;
-  const int kb1 = min(min(kb0 + kBlocksPerCta, p_last / BK), static_cast<int>(ldm));
+  const int kb0 = blockIdx.y * cta_blocks;
+  const int slice = kb0 / kBlocksPerCta;
+  const int kb1 = min(min(kb0 + cta_blocks, p_last / BK), static_cast<int>(ldm));
   if (kb0 >= kb1) return;                               // uniform over the CTA
 
   const int n = lane & 31, h = lane >> 5;
@@ -265,7 +253,7 @@ __global__ __launch_bounds__(256, (RW == 64) ? 3 : 2) void index_block_max_lds_k
 #pragma unroll
       for (int sp = 0; sp < NP; ++sp) {
         if (64 * sp + lane < nvalid)
-          PM[(static_cast<int64_t>(blockIdx.y) * cm_stride + slot0 + 64 * sp + lane) * kSlicePieces +
+          PM[(static_cast<int64_t>(slice) * cm_stride + slot0 + 64 * sp + lane) * kSlicePieces +
              (kb / kPieceBlocks) % kSlicePieces] = pmax[sp];
         pmax[sp] = -INFINITY;
       }
@@ -319,10 +307,12 @@ __global__ __launch_bounds__(256, (RW == 64) ? 3 : 2) void index_block_max_lds_k
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   }
-  // rows whose local block is at or below kb0 never read this entry
+  // a part of a slice leaves the slice's maximum to its piece maxima; rows
+  // whose local block is at or below kb0 never read this entry
+  if (!CM) return;
 #pragma unroll
   for (int sp = 0; sp < NP; ++sp)
-    if (64 * sp + lane < nvalid) CM[static_cast<int64_t>(blockIdx.y) * cm_stride + slot0 + 64 * sp + lane] = cmax[sp];
+    if (64 * sp + lane < nvalid) CM[static_cast<int64_t>(slice) * cm_stride + slot0 + 64 * sp + lane] = cmax[sp];
 }
 
 // ---------------------------------------------------------------- scores, per wave
@@ -335,7 +325,7 @@ constexpr int kSliceBlocks = 8;
 template <int D_IDX, int BK, bool PAGED>
 __global__ __launch_bounds__(256) void index_block_max_wave_kernel(
     const uint16_t* __restrict__ index_q, const uint16_t* __restrict__ index_k, msa_seqs sq,
-    const int32_t* __restrict__ unit_off, int H_kv, int qr, int64_t u0, int64_t u1, float* __restrict__ M,
+    int unit_shift, int H_kv, int qr, int64_t u0, int64_t u1, float* __restrict__ M,
     int64_t ldm) {
   constexpr int KS = D_IDX / 16;
   constexpr int MT = BK / 32;
@@ -343,7 +333,7 @@ __global__ __launch_bounds__(256) void index_block_max_wave_kernel(
   const int64_t uidx = u0 + blockIdx.y;
   const int slice = blockIdx.x * kWaves + threadIdx.x / kWave;
   if (uidx >= u1) return;
-  UnitRows ur = locate_unit(sq, unit_off, uidx, qr, 1);
+  UnitRows ur = locate_unit(sq, unit_shift, uidx, qr, 1);
   if (!ur.ok) return;
   const int p_last = ur.g.kv_len - ur.g.q_rows + ur.t0 + ur.nq - 1;
   if (p_last < 0) return;
@@ -450,7 +440,7 @@ __global__ __launch_bounds__(256) void index_block_max_wave_kernel(
 template <int D_IDX, int BK, int DEPTH, bool PAGED>
 __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
     const uint16_t* __restrict__ index_q, const uint16_t* __restrict__ index_k, msa_seqs sq,
-    const int32_t* __restrict__ unit_off, int H_kv, int qr, int64_t u0, int64_t u1, float* __restrict__ M,
+    int unit_shift, int H_kv, int qr, int64_t u0, int64_t u1, float* __restrict__ M,
     int64_t ldm) {
   constexpr int KS = D_IDX / 32;
   constexpr int HB = BK / 64;                         // 64-key sub-blocks per block
@@ -459,7 +449,7 @@ __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
   const int64_t uidx = u0 + blockIdx.y;
   const int slice = blockIdx.x * kWaves + threadIdx.x / kWave;
   if (uidx >= u1) return;
-  UnitRows ur = locate_unit(sq, unit_off, uidx, qr, 1);
+  UnitRows ur = locate_unit(sq, unit_shift, uidx, qr, 1);
   if (!ur.ok) return;
   const int p_last = ur.g.kv_len - ur.g.q_rows + ur.t0 + ur.nq - 1;
   if (p_last < 0) return;
@@ -758,16 +748,21 @@ __device__ __forceinline__ uint64_t scan_row_pruned(Load load, LoadCm cm, LoadPm
   return kb.list;
 }
 
+constexpr int kLaneBoundMaxK = 40;    // up to this k row_best_keys bounds a round by its 64 lane maxima
+
 // ---------------------------------------------------------------- radix selection
 // The largest t such that at least K of the wave's values x[0 .. V) (all
 // lanes; absent values are 0) are >= t: the K-th largest value when at least K
 // are present.  Bit by bit from the top, one compare per value and bit; the
 // counts are wave-uniform (ballot + popcount), so no value moves between lanes.
 // With LOBIT > 0 only bits 31 .. LOBIT are decided (the lower ones stay 0):
-// a lower bound of that value, within 2^LOBIT of it.
+// a lower bound of that value, within 2^LOBIT of it.  (Straight-line steps: a
+// loop that starts at the first differing bit and ends early runs half of them
+// but took 5 - 15 % longer.)
 template <int V, int LOBIT = 0>
 __device__ __forceinline__ uint32_t kth_largest_u32(const uint32_t* x, int K) {
   uint32_t t = 0;
+#pragma unroll
   for (int bit = 31; bit >= LOBIT; --bit) {
     const uint32_t c = t | (1u << bit);
     int n = 0;
@@ -775,6 +770,31 @@ __device__ __forceinline__ uint32_t kth_largest_u32(const uint32_t* x, int K) {
     for (int v = 0; v < V; ++v) n += __popcll(__ballot(x[v] >= c));
     if (n >= K) t = c;
   }
+  return t;
+}
+
+// The same down to a value that exactly K values reach, where the top 16 or 24
+// bits already tell the K-th largest from the next (*exact), else the K-th
+// largest itself.
+template <int V>
+__device__ __forceinline__ uint32_t kth_or_cut_u32(const uint32_t* x, int K, bool* exact) {
+  uint32_t t = 0;
+  int reach = 0;
+  auto steps = [&](auto from, auto to) {
+#pragma unroll
+    for (int bit = decltype(from)::value; bit >= decltype(to)::value; --bit) {
+      const uint32_t c = t | (1u << bit);
+      int n = 0;
+#pragma unroll
+      for (int v = 0; v < V; ++v) n += __popcll(__ballot(x[v] >= c));
+      t = n >= K ? c : t;
+      reach = n >= K ? n : reach;
+    }
+  };
+  steps(std::integral_constant<int, 31>{}, std::integral_constant<int, 16>{});
+  if (reach != K) steps(std::integral_constant<int, 15>{}, std::integral_constant<int, 8>{});
+  if (reach != K) steps(std::integral_constant<int, 7>{}, std::integral_constant<int, 0>{});
+  *exact = reach == K;
   return t;
 }
 
@@ -788,34 +808,43 @@ __device__ __forceinline__ uint32_t kth_largest_bound(const uint32_t* x, int nv,
   return kth_largest_u32<16, 16>(x, K);
 }
 
+// The float whose ordered value is t, for comparing scores directly (-inf and
+// everything below it: -inf, which every score reaches).
+__device__ __forceinline__ float ordered_to_float(uint32_t t) {
+  if (t <= 0x007FFFFFu) return -INFINITY;
+  return __uint_as_float((t & 0x80000000u) ? (t & 0x7FFFFFFFu) : ~t);
+}
+
 __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0));
 }
 
-// The K best of the cnt (<= 2 kWave) distinct non-zero keys in the wave's
-// LDS buffer `buf`: the K-th largest key kk is found by a radix search on the
-// score half, and on the id half among equal scores at the boundary; the keys
-// >= kk (all of them when cnt <= K) are compacted to the front of `buf` and
+// The K best of the cnt (<= 2 kWave) distinct non-zero keys c0 (lanes 0 ..
+// cnt-1) and c1 (lanes 0 .. cnt-65; absent keys are 0): a radix search on the
+// score half finds a value that exactly K keys reach, or the K-th largest
+// score, whose equals are then told apart by a search on the id half.  The
+// selected keys (all of them when cnt <= K) are compacted through `buf` and
 // returned one per lane in lanes 0 .. min(cnt, K)-1 (in no order; other
-// lanes 0).  With `kth` non-null, *kth receives kk (0 when cnt <= K).
-__device__ __forceinline__ uint64_t best_keys(uint64_t* buf, int cnt, int K, uint64_t* kth) {
+// lanes 0).  With `kth` non-null, *kth receives a key that exactly K keys
+// reach (0 when cnt <= K).
+__device__ __forceinline__ uint64_t best_of_keys(uint64_t c0, uint64_t c1, int cnt, int K, uint64_t* buf,
+                                                 uint64_t* kth) {
   const int lane = lane_id();
-  const uint64_t c0 = lane < cnt ? buf[lane] : 0ull;
-  const uint64_t c1 = kWave + lane < cnt ? buf[kWave + lane] : 0ull;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   uint64_t kk = 0;
   if (cnt > K) {
     uint32_t h[2] = {static_cast<uint32_t>(c0 >> 32), static_cast<uint32_t>(c1 >> 32)};
-    const uint32_t tv = kth_largest_u32<2>(h, K);
-    const int n_gt = __popcll(__ballot(h[0] > tv)) + __popcll(__ballot(h[1] > tv));
-    const int n_eq = __popcll(__ballot(h[0] == tv && c0 != 0ull)) + __popcll(__ballot(h[1] == tv && c1 != 0ull));
-    const int need = K - n_gt;                              // 1 <= need <= n_eq
+    bool exact;
+    const uint32_t tv = cnt <= kWave ? kth_or_cut_u32<1>(h, K, &exact) : kth_or_cut_u32<2>(h, K, &exact);
     kk = static_cast<uint64_t>(tv) << 32;
-    if (n_eq != need) {
-      uint32_t l[2] = {h[0] == tv && c0 != 0ull ? static_cast<uint32_t>(c0) : 0u,
-                       h[1] == tv && c1 != 0ull ? static_cast<uint32_t>(c1) : 0u};
-      kk |= kth_largest_u32<2>(l, need);
+    if (!exact) {
+      const int n_gt = __popcll(__ballot(h[0] > tv)) + __popcll(__ballot(h[1] > tv));
+      const int n_eq = __popcll(__ballot(h[0] == tv && c0 != 0ull)) + __popcll(__ballot(h[1] == tv && c1 != 0ull));
+      const int need = K - n_gt;                            // 1 <= need <= n_eq
+      if (n_eq != need) {
+        uint32_t l[2] = {h[0] == tv && c0 != 0ull ? static_cast<uint32_t>(c0) : 0u,
+                         h[1] == tv && c1 != 0ull ? static_cast<uint32_t>(c1) : 0u};
+        kk |= kth_largest_u32<2>(l, need);
+      }
     }
   }
   if (kth) *kth = kk;
@@ -830,6 +859,16 @@ __device__ __forceinline__ uint64_t best_keys(uint64_t* buf, int cnt, int K, uin
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   return list;
+}
+
+// The same of the cnt keys in the wave's LDS buffer `buf`.
+__device__ __forceinline__ uint64_t best_keys(uint64_t* buf, int cnt, int K, uint64_t* kth) {
+  const int lane = lane_id();
+  const uint64_t c0 = lane < cnt ? buf[lane] : 0ull;
+  const uint64_t c1 = kWave + lane < cnt ? buf[kWave + lane] : 0ull;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  return best_of_keys(c0, c1, cnt, K, buf, kth);
 }
 
 // Exact selection of a row through radix searches instead of sorting
@@ -879,11 +918,10 @@ __device__ __forceinline__ bool select_row_radix(const float* __restrict__ mrow,
         pv[kSlicePieces * kk + e] = kSlicePieces * ch + e < nval ? ordered_u32(x[e]) : 0u;
     }
   }
+  constexpr int kBuf = 2 * kWave;
   const uint32_t t1 = kth_largest_bound(pv, nv, K1);
   if (t1 == 0) return false;
-  // the float with ordered value t1 (scores compare against it directly)
-  const float t1f = __uint_as_float((t1 & 0x80000000u) ? (t1 & 0x7FFFFFFFu) : ~t1);
-  constexpr int kBuf = 2 * kWave;
+  const float t1f = ordered_to_float(t1);
   int cnt = 0;
   auto append = [&](bool take, float x, int b) {
     const uint64_t m = __ballot(take);
@@ -938,15 +976,20 @@ __device__ __forceinline__ bool select_row_radix(const float* __restrict__ mrow,
   return true;
 }
 
+// Stores the distinct ids of lanes 0 .. n-1 ascending in out[0 .. n), then -1
+// up to out[total) (n <= total <= kWave).
+__device__ __forceinline__ void store_ascending(uint32_t id, int n, int total, int32_t* __restrict__ out) {
+  const int lane = lane_id();
+  id = lane < n ? id : 0xFFFFFFFFu;
+  id = n <= 16 ? sort_asc_u32<16>(id) : (n <= 32 ? sort_asc_u32<32>(id) : sort_asc_u32<64>(id));
+  if (lane < total) out[lane] = static_cast<int32_t>(id);
+}
+
 // Local block + the K1 best keys of `list`, ids ascending, -1 padded.
 __device__ __forceinline__ void finish_row(uint64_t list, int K1, int lb, int topk, int32_t* __restrict__ out) {
   const int lane = lane_id();
   const int cnt = K1 > 0 ? __popcll(__ballot(lane < K1 && list != 0ull)) : 0;
-  uint32_t id = 0xFFFFFFFFu;
-  if (lane < cnt) id = key_block(list);
-  else if (lane == cnt) id = static_cast<uint32_t>(lb);
-  id = wave_sort_asc_u32(id);
-  if (lane < topk) out[lane] = lane <= cnt ? static_cast<int32_t>(id) : -1;
+  store_ascending(lane < cnt ? key_block(list) : static_cast<uint32_t>(lb), cnt + 1, topk, out);
 }
 
 struct RowTask {
@@ -961,7 +1004,7 @@ struct RowTask {
 // Task `task` of a chunk: index row L = task % rpu of unit u0 + task / rpu,
 // where rpu (<= U * 64) bounds the index rows a unit can hold.
 __device__ __forceinline__ RowTask locate_row(const float* __restrict__ M, int64_t ldm, const msa_seqs& sq,
-                                              const int32_t* __restrict__ unit_off, int H_kv, int qr, int U,
+                                              int unit_shift, int H_kv, int qr, int U,
                                               int rpu, int64_t u0, int64_t task, int BK, int topk,
                                               int32_t* __restrict__ block_ids) {
   RowTask t;
@@ -974,7 +1017,7 @@ __device__ __forceinline__ RowTask locate_row(const float* __restrict__ M, int64
   const int64_t uidx = u0 + uq;
   const int L = static_cast<int>(tk - uq * static_cast<uint32_t>(rpu));   // index row inside the unit
   const int64_t slot = (uidx - u0) * (static_cast<int64_t>(U) * kWave) + L;
-  UnitRows ur = locate_unit(sq, unit_off, uidx, qr, U);
+  UnitRows ur = locate_unit(sq, unit_shift, uidx, qr, U);
   if (!ur.ok || L >= ur.nq * H_kv) return t;
   const int row = ur.t0 + (L >> __builtin_ctz(H_kv));
   const int r = L & (H_kv - 1);
@@ -992,19 +1035,23 @@ __device__ __forceinline__ RowTask locate_row(const float* __restrict__ M, int64
   return t;
 }
 
-// One wave per index row.  With chunk maxima (CM[chunk][row], row stride
-// cm_stride) the row is ranked by the pruned scan.
+template <bool VEC, int RP>
+__device__ __forceinline__ uint64_t row_best_keys(const float* __restrict__ srow, int n, int k, uint64_t* buf);
+__device__ __forceinline__ uint64_t short_row_best_keys(const float* __restrict__ srow, int n, int K, uint64_t* buf);
+
+// One wave per index row.  With piece maxima (and chunk maxima
+// CM[chunk][row], row stride cm_stride) the row is ranked from those.
 __global__ __launch_bounds__(256) void index_topk_kernel(
     const float* __restrict__ M, int64_t ldm, const float* __restrict__ CM, int64_t cm_stride,
     const float* __restrict__ PM, msa_seqs sq,
-    const int32_t* __restrict__ unit_off, int H_kv, int qr, int U, int rpu, int64_t u0, int64_t u1, int BK,
+    int unit_shift, int H_kv, int qr, int U, int rpu, int64_t u0, int64_t u1, int BK,
     int topk, int32_t* __restrict__ block_ids) {
   __shared__ uint64_t s_pend[kWaves][2 * kWave];
   __shared__ int32_t s_surv[kWaves][kSurvivorCap];
   const int lane = lane_id();
   const int64_t task = static_cast<int64_t>(blockIdx.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x) / kWave;
   if (task >= (u1 - u0) * rpu) return;
-  const RowTask t = locate_row(M, ldm, sq, unit_off, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
+  const RowTask t = locate_row(M, ldm, sq, unit_shift, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
   if (!t.ok) return;
   if (t.no_position) {
     if (lane < topk) t.out[lane] = -1;
@@ -1016,13 +1063,33 @@ __global__ __launch_bounds__(256) void index_topk_kernel(
   kb.pend = s_pend[threadIdx.x / kWave];
   kb.K1 = topk - 1;
   uint64_t list;
-  if (CM) {
-    const float* cmrow = CM + t.slot;
-    auto cm = [=](int c) { return cmrow[static_cast<int64_t>(c) * cm_stride]; };
+  if (PM) {
     const float* pmrow = PM + t.slot * kSlicePieces;
     auto pm = [=](int q) { return pmrow[static_cast<int64_t>(q / kSlicePieces) * cm_stride * kSlicePieces + q % kSlicePieces]; };
+    const int npiece = (t.nscan + kPieceBlocks - 1) / kPieceBlocks;
     auto pm4 = [=](int ch) { return *reinterpret_cast<const f32x4*>(pmrow + static_cast<int64_t>(ch) * cm_stride * kSlicePieces); };
-    if (!select_row_radix(mrow, pm4, t.nscan, topk - 1, kb.pend, s_surv[threadIdx.x / kWave], list))
+    // chunk maxima, or where CTAs scored pieces the maxima of a chunk's pieces
+    auto cm = [=](int c) {
+      if (CM) return CM[t.slot + static_cast<int64_t>(c) * cm_stride];
+      const f32x4 x = pm4(c);
+      float m = x[0];
+#pragma unroll
+      for (int e = 1; e < kSlicePieces; ++e) m = kSlicePieces * c + e < npiece ? fmaxf(m, x[e]) : m;
+      return m;
+    };
+    // Rows of at most 128 blocks are ranked from registers.  Short rows are
+    // read whole: the piece maxima bound little when there are not many more
+    // pieces than ids to pick (32768 x 8 rows of up to 511 blocks, k 32: 32
+    // pieces for 31 ids, and the candidates overflow the buffer; 357 -> 216 us).
+    const int K1 = topk - 1;
+    uint64_t* buf = kb.pend;
+    if (K1 > 0 && t.nscan > K1 && t.nscan <= 2 * kWave) {
+      list = short_row_best_keys(mrow, t.nscan, K1, buf);
+    } else if (K1 > 0 && t.nscan > K1 && t.nscan <= 8 * kWave)
+      list = row_best_keys<true, 8>(mrow, t.nscan, K1, buf);
+    else if (K1 > 0 && t.nscan > K1 && t.nscan <= 16 * kWave && t.nscan <= 2 * kPieceBlocks * K1)
+      list = row_best_keys<true, 16>(mrow, t.nscan, K1, buf);
+    else if (!select_row_radix(mrow, pm4, t.nscan, topk - 1, kb.pend, s_surv[threadIdx.x / kWave], list))
       list = scan_row_pruned(load, cm, pm, t.nscan, kb, s_surv[threadIdx.x / kWave]);
   } else {
     list = scan_row_batched(load, t.nscan, kb);
@@ -1036,14 +1103,14 @@ __global__ __launch_bounds__(256) void index_topk_kernel(
 constexpr int kSplitWaves = 16;
 
 __global__ __launch_bounds__(64 * kSplitWaves) void index_topk_split_kernel(
-    const float* __restrict__ M, int64_t ldm, msa_seqs sq, const int32_t* __restrict__ unit_off, int H_kv,
+    const float* __restrict__ M, int64_t ldm, msa_seqs sq, int unit_shift, int H_kv,
     int qr, int U, int rpu, int64_t u0, int64_t u1, int BK, int topk, int32_t* __restrict__ block_ids) {
   __shared__ uint64_t lists[kSplitWaves][kWave];
   const int lane = lane_id();
   const int w = threadIdx.x / kWave;
   const int64_t task = blockIdx.x;
   if (task >= (u1 - u0) * rpu) return;              // uniform over the CTA
-  const RowTask t = locate_row(M, ldm, sq, unit_off, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
+  const RowTask t = locate_row(M, ldm, sq, unit_shift, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
   if (!t.ok) return;                                 // uniform
   if (t.no_position) {
     if (w == 0 && lane < topk) t.out[lane] = -1;
@@ -1073,8 +1140,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void index_topk_split_kernel(
 // The row is read in rounds of RP values per lane (VEC: float4 loads; the
 // row is 16-byte aligned and a load that starts below n stays inside its
 // allocation).  A round's bound is the k-th largest of the lanes' maxima (k
-// distinct lanes hold a score at least that large), raised to the running
-// bound; the round's scores at or above it are appended as keys to the
+// distinct lanes hold a score at least that large; for large k of the lane
+// halves' maxima), raised to the running bound; the round's scores at or above it are appended as keys to the
 // wave's LDS buffer `buf` (2 kWave entries).  A buffer more than half full
 // is cut to its k best, whose k-th key raises the bound.  The k best keys of
 // the buffer are the row's.  A row whose candidates still overflow the
@@ -1102,20 +1169,33 @@ __device__ __forceinline__ uint64_t row_best_keys(const float* __restrict__ srow
 #pragma unroll
       for (int v = 0; v < RP; ++v) x[v] = col_of(v) < n ? srow[col_of(v)] : 0.f;
     }
-    uint32_t lm = 0;
+    // the maxima of two halves of the lane's values (two of every four, so
+    // that both hold values in short rows); absent columns do not count
+    const bool full = c0 + kWave * RP <= n;
+    float mf[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-    for (int v = 0; v < RP; ++v) {
-      const uint32_t o = col_of(v) < n ? ordered_u32(x[v]) : 0u;
-      lm = o > lm ? o : lm;
+    for (int v = 0; v < RP; ++v)
+      mf[(v >> 1) & 1] = fmaxf(mf[(v >> 1) & 1], full || col_of(v) < n ? x[v] : -INFINITY);
+    // the k-th largest of the lanes' maxima, for large k of the halves' (the
+    // 64th of 64 lanes bounds little: a quarter of 1024 scores reach it), to
+    // its top 16 bits (a lower bound: half the search steps; the cut below
+    // raises the bound)
+    uint32_t lm[2];
+    uint32_t tr;
+    if (k <= kLaneBoundMaxK) {
+      lm[0] = full || col_of(0) < n ? ordered_u32(fmaxf(mf[0], mf[1])) : 0u;
+      tr = kth_largest_u32<1, 16>(lm, k);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) lm[e] = full || col_of(2 * e) < n ? ordered_u32(mf[e]) : 0u;
+      tr = kth_largest_u32<2, 16>(lm, k);
     }
-    // the k-th largest lane maximum to its top 16 bits (a lower bound: half
-    // the search steps; the cut below raises the bound exactly)
-    const uint32_t tr = kth_largest_u32<1, 16>(&lm, k);
     t = tr > t ? tr : t;
+    const float tf = ordered_to_float(t);
 #pragma unroll
     for (int v = 0; v < RP; ++v) {
       const int c = col_of(v);
-      const bool take = c < n && ordered_u32(x[v]) >= t;
+      const bool take = x[v] >= tf && (full || c < n);
       const uint64_t m = __ballot(take);
       if (m == 0) continue;
       const int pos = cnt + lanes_below(m);
@@ -1153,14 +1233,14 @@ __device__ __forceinline__ uint64_t row_best_keys(const float* __restrict__ srow
 constexpr int kRowWaves = 4;
 
 __global__ __launch_bounds__(kRowWaves * kWave) void index_topk_rows_kernel(
-    const float* __restrict__ M, int64_t ldm, msa_seqs sq, const int32_t* __restrict__ unit_off, int H_kv, int qr,
+    const float* __restrict__ M, int64_t ldm, msa_seqs sq, int unit_shift, int H_kv, int qr,
     int U, int rpu, int64_t u0, int64_t u1, int BK, int topk, int32_t* __restrict__ block_ids) {
   __shared__ uint64_t s_buf[kRowWaves][2 * kWave];
   const int lane = lane_id();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x) / kWave;
   const int64_t task = static_cast<int64_t>(blockIdx.x) * kRowWaves + w;
   if (task >= (u1 - u0) * rpu) return;
-  const RowTask t = locate_row(M, ldm, sq, unit_off, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
+  const RowTask t = locate_row(M, ldm, sq, unit_shift, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
   if (!t.ok) return;
   if (t.no_position) {
     if (lane < topk) t.out[lane] = -1;
@@ -1172,9 +1252,17 @@ __global__ __launch_bounds__(kRowWaves * kWave) void index_topk_rows_kernel(
   finish_row(list, K1, t.lb, topk, t.out);
 }
 
+// The min(n, K) best of n scores, n <= 2 kWave, from registers.
+__device__ __forceinline__ uint64_t short_row_best_keys(const float* __restrict__ srow, int n, int K, uint64_t* buf) {
+  const int lane = lane_id();
+  const uint64_t c0 = lane < n ? rank_key(srow[lane], static_cast<uint32_t>(lane)) : 0ull;
+  const uint64_t c1 = kWave + lane < n ? rank_key(srow[kWave + lane], static_cast<uint32_t>(kWave + lane)) : 0ull;
+  return best_of_keys(c0, c1, n, K, buf, nullptr);
+}
+
 // The Top-k operator on its own (msa_block_topk): the k best columns of each
-// row of an fp32 score matrix, one wave per row, by row_best_keys with
-// rounds of 16 values per lane for rows of at most 1024 columns, else 32.
+// row of an fp32 score matrix, one wave per row, from registers (RP = 2: at
+// most 128 columns) or by row_best_keys with rounds of RP values per lane.
 template <bool VEC, int RP>
 __global__ __launch_bounds__(kRowWaves * kWave) void row_topk_kernel(const float* __restrict__ scores,
                                                                      int64_t n_rows, int n_cols, int64_t ld, int k,
@@ -1184,11 +1272,12 @@ __global__ __launch_bounds__(kRowWaves * kWave) void row_topk_kernel(const float
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x) / kWave;
   const int64_t row = static_cast<int64_t>(blockIdx.x) * kRowWaves + w;
   if (row >= n_rows) return;
-  const uint64_t list = row_best_keys<VEC, RP>(scores + row * ld, n_cols, k, s_buf[w]);
-  const int nsel = __popcll(__ballot(lane < k && list != 0ull));
-  uint32_t id = lane < nsel ? key_block(list) : 0xFFFFFFFFu;
-  id = wave_sort_asc_u32(id);
-  if (lane < k) ids[row * k + lane] = lane < nsel ? static_cast<int32_t>(id) : -1;
+  uint64_t list;
+  if constexpr (RP == 2)
+    list = short_row_best_keys(scores + row * ld, n_cols, k, s_buf[w]);
+  else
+    list = row_best_keys<VEC, RP>(scores + row * ld, n_cols, k, s_buf[w]);
+  store_ascending(key_block(list), __popcll(__ballot(lane < k && list != 0ull)), k, ids + row * k);
 }
 
 // ---------------------------------------------------------------- host side
@@ -1201,7 +1290,7 @@ struct IndexPlan {
   int bcap;             // M row length (key blocks, multiple of 4)
   int cmcap;            // chunk maxima per row (64-block Top-k chunks; U = 4 only, else 0)
   int pcap;             // piece maxima per row (16-block pieces; with chunk maxima only)
-  size_t hdr_bytes;
+  size_t hdr_bytes;     // unused bytes in front of the scores (part of the workspace's stated size)
   size_t unit_bytes;    // M and chunk-maximum bytes per unit
 };
 
@@ -1221,7 +1310,7 @@ int make_plan(const msa_seqs* seqs, int H_kv, int d_idx, int BK, int topk, Index
   const int64_t mq = seqs->max_q_rows;
   pl->U = mq > 4 * pl->qr && d_idx == 64 && BK == 64 ? 2 * kWaves : (mq > 2 * pl->qr ? kWaves : 1);
   pl->narrow = pl->U == 1 && std::min(pl->qr, seqs->max_q_rows) * H_kv <= 16;
-  // at most one row group per sequence: unit s is sequence s, no unit table
+  // at most one row group per sequence: unit s is sequence s
   pl->seq_units = pl->U == 1 && seqs->max_q_rows <= pl->qr;
   const int64_t max_groups = seqs->total_q_rows / pl->qr + seqs->num_seqs;
   pl->max_units = pl->seq_units ? seqs->num_seqs : max_groups / pl->U + seqs->num_seqs;
@@ -1234,6 +1323,7 @@ int make_plan(const msa_seqs* seqs, int H_kv, int d_idx, int BK, int topk, Index
   return MSA_OK;
 }
 
+constexpr int64_t kMinScoreCtas = 1024;                  // fewer slices: CTAs take pieces of them
 constexpr size_t kDefaultScoreBytes = size_t(4) << 30;   // block-score staging per call
 constexpr int64_t kSplitTopkRows = 4096;                 // fewer index rows: no chunk / piece maxima
 // Few rows go one wave per row (index_topk_rows_kernel) when the rows are
@@ -1251,38 +1341,38 @@ constexpr int kNarrowDepth = D == 64 ? 4 : 2;
 
 template <int D, int B, bool PAGED>
 void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const uint16_t* iq, const uint16_t* ik,
-                      const msa_seqs& sq, const int32_t* unit_off, int H_kv, int64_t u0, int64_t u1, float* M,
+                      const msa_seqs& sq, int unit_shift, int H_kv, int64_t u0, int64_t u1, int cta_blocks, float* M,
                       float* CM, int64_t cm_stride, float* PM) {
   if constexpr (D == 64 && B == 64) {
     if (pl.U == 2 * kWaves) {
       msa_prof::launch("index_block_max_lds_kernel", (index_block_max_lds_kernel<D, B, 128, PAGED>), grid, dim3(256),
-                       0, stream, iq, ik, sq, unit_off, H_kv, pl.qr, u0, u1, M, static_cast<int64_t>(pl.bcap), CM,
+                       0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, cta_blocks, M, static_cast<int64_t>(pl.bcap), CM,
                        cm_stride, PM);
       return;
     }
   }
   if (pl.U == kWaves)
     msa_prof::launch("index_block_max_lds_kernel", (index_block_max_lds_kernel<D, B, 64, PAGED>), grid, dim3(256), 0,
-                     stream, iq, ik, sq, unit_off, H_kv, pl.qr, u0, u1, M, static_cast<int64_t>(pl.bcap), CM,
+                     stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, cta_blocks, M, static_cast<int64_t>(pl.bcap), CM,
                      cm_stride, PM);
   else if (pl.narrow)
     msa_prof::launch("index_block_max_narrow_kernel", (index_block_max_narrow_kernel<D, B, kNarrowDepth<D, B>, PAGED>),
-                     grid, dim3(256), 0, stream, iq, ik, sq, unit_off, H_kv, pl.qr, u0, u1, M,
+                     grid, dim3(256), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
                      static_cast<int64_t>(pl.bcap));
   else
     msa_prof::launch("index_block_max_wave_kernel", (index_block_max_wave_kernel<D, B, PAGED>), grid, dim3(256), 0,
-                     stream, iq, ik, sq, unit_off, H_kv, pl.qr, u0, u1, M, static_cast<int64_t>(pl.bcap));
+                     stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M, static_cast<int64_t>(pl.bcap));
 }
 
 // A paged key side runs the kernels instantiated for it.
 template <int D, int B>
 void launch_scores(const IndexPlan& pl, dim3 grid, hipStream_t stream, const uint16_t* iq, const uint16_t* ik,
-                   const msa_seqs& sq, const int32_t* unit_off, int H_kv, int64_t u0, int64_t u1, float* M,
+                   const msa_seqs& sq, int unit_shift, int H_kv, int64_t u0, int64_t u1, int cta_blocks, float* M,
                    float* CM, int64_t cm_stride, float* PM) {
   if (sq.block_table)
-    launch_scores_as<D, B, true>(pl, grid, stream, iq, ik, sq, unit_off, H_kv, u0, u1, M, CM, cm_stride, PM);
+    launch_scores_as<D, B, true>(pl, grid, stream, iq, ik, sq, unit_shift, H_kv, u0, u1, cta_blocks, M, CM, cm_stride, PM);
   else
-    launch_scores_as<D, B, false>(pl, grid, stream, iq, ik, sq, unit_off, H_kv, u0, u1, M, CM, cm_stride, PM);
+    launch_scores_as<D, B, false>(pl, grid, stream, iq, ik, sq, unit_shift, H_kv, u0, u1, cta_blocks, M, CM, cm_stride, PM);
 }
 
 }  // namespace
@@ -1307,7 +1397,7 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
   int64_t chunk = static_cast<int64_t>((workspace_bytes - pl.hdr_bytes) / pl.unit_bytes);
   if (chunk > pl.max_units) chunk = pl.max_units;
 
-  int32_t* unit_off = pl.seq_units ? nullptr : static_cast<int32_t*>(workspace);
+  const int unit_shift = pl.seq_units ? -1 : __builtin_ctz(static_cast<unsigned>(pl.qr * pl.U));
   float* M = reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.hdr_bytes);
   // chunk maxima CM[chunk][row] follow the chunk's score rows
   const int64_t cm_stride = chunk * pl.U * kWave;
@@ -1318,25 +1408,27 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
   const uint16_t* iq = static_cast<const uint16_t*>(index_q);
   const uint16_t* ik = static_cast<const uint16_t*>(index_k);
 
-  if (unit_off)
-    msa_prof::launch("unit_offsets_kernel", unit_offsets_kernel, dim3(1), dim3(256), 0, stream, sq, pl.qr, pl.U,
-                     unit_off);
   // per-wave kernel: slices of kSliceBlocks consecutive blocks, 4 per CTA
   const int nslice = (pl.bcap + kSliceBlocks - 1) / kSliceBlocks;
-  const unsigned ny = static_cast<unsigned>((pl.bcap + kBlocksPerCta - 1) / kBlocksPerCta);
   for (int64_t u0 = 0; u0 < pl.max_units; u0 += chunk) {
     const int64_t u1 = u0 + chunk < pl.max_units ? u0 + chunk : pl.max_units;
+    // a CTA scores a 64-block slice, or a 16-block piece where slices would
+    // leave CUs idle (16 CTAs for 4096 rows of 2 groups: 55 us against 20)
+    const int64_t slices = (pl.bcap + kBlocksPerCta - 1) / kBlocksPerCta;
+    const int cta_blocks = (u1 - u0) * slices < kMinScoreCtas ? kPieceBlocks : kBlocksPerCta;
+    const unsigned ny = static_cast<unsigned>((pl.bcap + cta_blocks - 1) / cta_blocks);
+    float* cm = cta_blocks == kBlocksPerCta ? CM : nullptr;
     const dim3 grid = pl.U >= kWaves ? dim3(static_cast<unsigned>(u1 - u0), ny)
                                      : dim3(static_cast<unsigned>((nslice + kWaves - 1) / kWaves),
                                             static_cast<unsigned>(u1 - u0));
     if (d_idx == 64 && block_size == 64)
-      launch_scores<64, 64>(pl, grid, stream, iq, ik, sq, unit_off, num_kv_heads, u0, u1, M, CM, cm_stride, PM);
+      launch_scores<64, 64>(pl, grid, stream, iq, ik, sq, unit_shift, num_kv_heads, u0, u1, cta_blocks, M, cm, cm_stride, PM);
     else if (d_idx == 64)
-      launch_scores<64, 128>(pl, grid, stream, iq, ik, sq, unit_off, num_kv_heads, u0, u1, M, CM, cm_stride, PM);
+      launch_scores<64, 128>(pl, grid, stream, iq, ik, sq, unit_shift, num_kv_heads, u0, u1, cta_blocks, M, cm, cm_stride, PM);
     else if (block_size == 64)
-      launch_scores<128, 64>(pl, grid, stream, iq, ik, sq, unit_off, num_kv_heads, u0, u1, M, CM, cm_stride, PM);
+      launch_scores<128, 64>(pl, grid, stream, iq, ik, sq, unit_shift, num_kv_heads, u0, u1, cta_blocks, M, cm, cm_stride, PM);
     else
-      launch_scores<128, 128>(pl, grid, stream, iq, ik, sq, unit_off, num_kv_heads, u0, u1, M, CM, cm_stride, PM);
+      launch_scores<128, 128>(pl, grid, stream, iq, ik, sq, unit_shift, num_kv_heads, u0, u1, cta_blocks, M, cm, cm_stride, PM);
     // index rows a unit can hold: its query rows (<= U * qr, <= max_q_rows) x H_kv
     const int rpu = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(pl.U) * pl.qr, seqs->max_q_rows)) *
                     num_kv_heads;
@@ -1345,17 +1437,17 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
     if (rows <= kSplitTopkRows && topk <= kRowTopkMaxK && rows >= kRowTopkMinRows && pl.bcap <= kRowTopkMaxBlocks)
       msa_prof::launch("index_topk_rows_kernel", index_topk_rows_kernel,
                        dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), dim3(kRowWaves * kWave), 0,
-                       stream, M, static_cast<int64_t>(pl.bcap), sq, unit_off, num_kv_heads, pl.qr, pl.U, rpu, u0, u1,
+                       stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0, u1,
                        block_size, topk, block_ids);
     else if (rows <= kSplitTopkRows)
       msa_prof::launch("index_topk_split_kernel", index_topk_split_kernel, dim3(static_cast<unsigned>(rows)),
-                       dim3(64 * kSplitWaves), 0, stream, M, static_cast<int64_t>(pl.bcap), sq, unit_off,
+                       dim3(64 * kSplitWaves), 0, stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift,
                        num_kv_heads, pl.qr, pl.U, rpu, u0, u1, block_size, topk, block_ids);
     else
       msa_prof::launch("index_topk_kernel", index_topk_kernel, dim3(static_cast<unsigned>((rows + kWaves - 1) / kWaves)),
-                       dim3(256), 0, stream, M, static_cast<int64_t>(pl.bcap), static_cast<const float*>(CM), cm_stride,
+                       dim3(256), 0, stream, M, static_cast<int64_t>(pl.bcap), static_cast<const float*>(cm), cm_stride,
                        static_cast<const float*>(PM),
-                       sq, unit_off, num_kv_heads, pl.qr, pl.U, rpu, u0, u1, block_size, topk, block_ids);
+                       sq, unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0, u1, block_size, topk, block_ids);
   }
   return msa_host::launch_status();
 }
@@ -1386,17 +1478,22 @@ extern "C" int msa_block_topk(const float* scores, int64_t n_rows, int n_cols, i
   const int64_t grid = (n_rows + kRowWaves - 1) / kRowWaves;
   if (grid > 0x7FFFFFFF) return MSA_ERR_UNSUPPORTED;
   const bool vec = reinterpret_cast<uintptr_t>(scores) % 16 == 0 && ld % 4 == 0;
-  auto launch_row_topk = [&](auto k16, auto k32) {
-    const dim3 g(static_cast<unsigned>(grid)), b(kRowWaves * kWave);
-    if (n_cols <= 16 * kWave)
-      msa_prof::launch("row_topk_kernel", k16, g, b, 0, stream, scores, n_rows, n_cols, ld, k, ids);
-    else
-      msa_prof::launch("row_topk_kernel", k32, g, b, 0, stream, scores, n_rows, n_cols, ld, k, ids);
+  // the fewest values per lane that hold a row in one round, up to 32
+  // (300000 x 256, k 8: 176 us in rounds of 16 per lane, 130 in rounds of 4)
+  auto run = [&](auto kernel) {
+    msa_prof::launch("row_topk_kernel", kernel, dim3(static_cast<unsigned>(grid)), dim3(kRowWaves * kWave), 0, stream,
+                     scores, n_rows, n_cols, ld, k, ids);
   };
-  if (vec)
-    launch_row_topk(row_topk_kernel<true, 16>, row_topk_kernel<true, 32>);
-  else
-    launch_row_topk(row_topk_kernel<false, 16>, row_topk_kernel<false, 32>);
+  auto by_width = [&](auto v) {
+    constexpr bool V = decltype(v)::value;
+    if (n_cols <= 2 * kWave) run(row_topk_kernel<false, 2>);
+    else if (n_cols <= 4 * kWave) run(row_topk_kernel<V, 4>);
+    else if (n_cols <= 8 * kWave) run(row_topk_kernel<V, 8>);
+    else if (n_cols <= 16 * kWave) run(row_topk_kernel<V, 16>);
+    else run(row_topk_kernel<V, 32>);
+  };
+  if (vec) by_width(std::true_type{});
+  else by_width(std::false_type{});
   return msa_host::launch_status();
 }
 

@@ -115,16 +115,26 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Value of lane (lane ^ J): DPP quad permutes for J = 1, 2, ds_swizzle
-// (bit-mask mode, within 32 lanes) for J = 4, 8, 16, permlane32 swap for 32.
+// Value of lane (lane ^ J), all in the vector ALU: DPP quad permutes for J = 1,
+// 2, a half-row mirror and a quad mirror for 4, a row rotation for 8, permlane
+// swaps for 16 and 32.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xF, 0xF, false));
+}
 template <int J>
 __device__ __forceinline__ uint32_t xor_lane_u32(uint32_t v) {
   if constexpr (J == 1) {
-    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0xB1, 0xF, 0xF, false));
+    return dpp_u32<0xB1>(v);
   } else if constexpr (J == 2) {
-    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x4E, 0xF, 0xF, false));
-  } else if constexpr (J < 32) {
-    return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(static_cast<int>(v), 0x1F | (J << 10)));
+    return dpp_u32<0x4E>(v);
+  } else if constexpr (J == 4) {
+    return dpp_u32<0x1B>(dpp_u32<0x141>(v));
+  } else if constexpr (J == 8) {
+    return dpp_u32<0x128>(v);
+  } else if constexpr (J == 16) {
+    auto sw = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (__lane_id() & 16) == 0 ? sw[1] : sw[0];
   } else {
     auto sw = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     return __lane_id() < 32 ? sw[1] : sw[0];
@@ -199,20 +209,21 @@ __device__ __forceinline__ uint64_t wave_bitonic_merge_desc_u64(uint64_t v) {
   // K = 128 > every lane index: all lanes sort descending
   return bitonic_stage_desc_u64<128, kWave / 2>(v);
 }
-// Bitonic sort of one uint32 per lane, ascending.
-__device__ __forceinline__ uint32_t wave_sort_asc_u32(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int k = 2; k <= kWave; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), j));
-      bool asc_block = (lane & k) == 0;
-      bool lower = (lane & j) == 0;
-      bool take_min = (asc_block == lower);
-      v = take_min ? (v < o ? v : o) : (v > o ? v : o);
-    }
+// Bitonic sort of one uint32 per lane, ascending within each group of N lanes.
+template <int K, int J>
+__device__ __forceinline__ uint32_t sort_stage_u32(uint32_t v, bool up) {
+  if constexpr (J == 0) {
+    return v;
+  } else {
+    const uint32_t o = xor_lane_u32<J>(v);
+    v = ((__lane_id() & J) == 0) == up ? (v < o ? v : o) : (v > o ? v : o);
+    return sort_stage_u32<K, J / 2>(v, up);
   }
+}
+template <int N, int K = 2>
+__device__ __forceinline__ uint32_t sort_asc_u32(uint32_t v) {
+  v = sort_stage_u32<K, K / 2>(v, K == N || (__lane_id() & K) == 0);
+  if constexpr (K < N) v = sort_asc_u32<N, 2 * K>(v);
   return v;
 }
 

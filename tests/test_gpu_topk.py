@@ -14,6 +14,7 @@ import torch
 
 import oracle.msa_oracle as O
 from paper_2606_13392_amd import msa, synth
+from tests.util import check_block_ids, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +98,51 @@ def test_block_topk_paper_shapes(shape):
     x.scatter_(1, g, -INF)
     assert bool((low >= x.amax(dim=1)).all())
     _say(f"[block_topk] N {N}: {rows.size} rows exact, {N} rows valid")
+
+
+@pytest.mark.parametrize("ld_pad", [0, 1])
+@pytest.mark.parametrize("k", [1, 16, 40, 41, 63, 64])
+def test_block_topk_row_widths(k, ld_pad):
+    """Widths around each kernel variant's limit (rows in registers up to 128
+    columns, rounds of 256, 512, 1024 and 2048) and k around the one from which
+    a round is bounded by the lane halves' maxima: N(0, 1) rows and rows of few
+    distinct values; ids equal the oracle's."""
+    for B in (1, 64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 2049):
+        rng = np.random.default_rng([B, k, ld_pad])
+        x = rng.standard_normal((24, B)).astype(np.float32)
+        x[12:] = rng.choice(np.array(POOL, dtype=np.float32), size=(12, B))
+        buf = torch.zeros((24, B + ld_pad), device="cuda")
+        buf[:, :B] = torch.from_numpy(x).to("cuda")
+        ids = msa.block_topk(buf[:, :B], k).cpu().numpy()
+        assert np.array_equal(ids, O.row_topk(x, k)), f"{B} columns, k {k}"
+
+
+# name, rows, keys, H_kv, block, topk, equal keys
+INDEX_CASES = [
+    # few units: CTAs score 16-block pieces and write no slice maxima
+    ("pieces_edge_of_slice", [130, 40], [64 * 64 + 1, 65 * 64], 2, 64, 16, False),
+    ("pieces_ties_pruned_scan", [140], [1100 * 64], 1, 64, 8, True),
+    ("rows_of_127_to_129_blocks", [200], [129 * 128 + 5], 4, 128, 40, False),
+    ("rows_of_511_to_513_blocks", [140], [513 * 64 + 40], 2, 64, 64, False),
+    ("rows_of_1023_to_1025_blocks", [140], [1025 * 64 + 40], 2, 64, 33, False),
+    ("units_of_many_sequences", [33, 0, 70, 1, 129, 64, 65] * 10, [300, 5, 900, 64, 129, 64, 2000] * 10, 8, 64, 5, False),
+]
+
+
+@pytest.mark.parametrize("case", INDEX_CASES, ids=[c[0] for c in INDEX_CASES])
+def test_index_topk_paths(case):
+    name, rows, keys, H_kv, bk, topk, equal = case
+    p = synth.packed_problem(name, rows, keys, num_q_heads=H_kv, num_kv_heads=H_kv, block_size=bk, topk=topk,
+                             seed=zlib.crc32(name.encode()) % 10000)
+    x = synth.generate_numpy(p)
+    if equal:
+        x["index_k"][:] = x["index_k"][:1]
+    lay = O.layout_of(p)
+    pick = sorted(set(range(p.total_q_rows)) & set(np.linspace(0, p.total_q_rows - 1, 60).astype(int).tolist()))
+    seqs = msa.Seqs.from_problem(p, torch.device("cuda"))
+    ids = msa.index_topk(to_dev(x["index_q"]), to_dev(x["index_k"]), seqs, bk, topk).cpu().numpy()[pick]
+    want, gaps = O.select_blocks(x["index_q"], x["index_k"], lay, bk, topk, rows=pick)
+    if equal:
+        assert np.array_equal(ids, want)
+    else:
+        check_block_ids(ids, want, gaps, x, lay, bk, topk, rows=pick)
