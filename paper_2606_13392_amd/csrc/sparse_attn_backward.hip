@@ -19,8 +19,8 @@
 //   bwd_delta        D per (row, head)
 //   per chunk of query rows:
 //     reverse index  (kvo_index.h)
-//     bwd_kvo        persistent CTAs of B_k / 16 waves (two CTAs per CU at
-//                    B_k 64, one at 128) over the work items (<= 256 queries
+//     bwd_kvo        persistent CTAs of 4 waves, two per CU (B_k 128: 8 waves,
+//                    one per CU, see below) over the work items (<= 256 queries
 //                    of one tile).  K and V of the block sit in LDS row-major
 //                    (K's 16-byte segments permuted per row).
 //                    A pass takes 32 gathered (query, head) rows, whose Q and
@@ -43,17 +43,15 @@
 
 namespace {
 
-// Key blocks of 64 or 128 keys: one wave per 16 keys (4 or 8 waves per CTA).
-template <int BK>
-constexpr int bwd_waves() { return BK / 16; }
-template <int BK>
-constexpr int bwd_threads() { return 64 * bwd_waves<BK>(); }
+// 64-key blocks: one wave per 16 keys.
+constexpr int kBwdWaves = 4;
+constexpr int kBwdThreads = 64 * kBwdWaves;
 constexpr int kBwdPassRows = 32;                      // gathered (query, head) rows per CTA pass
 template <int BK>
 constexpr int bwd_part_floats() { return 2 * BK * kHeadDim; }   // dK and dV of one work item
 
-template <int BK>
 struct BwdSmem {
+  static constexpr int BK = 64;
   uint16_t k[BK][kHeadDim];                           // K block, 256-byte rows, segments swizzled (bwd_swz)
   uint16_t v[BK][kHeadDim + 8];                       // V block, row-major
   // Q and dO rows of a pass (double-buffered), row-major with 16-byte
@@ -68,9 +66,7 @@ struct BwdSmem {
   int32_t s_row[kItemQueries];                        // query row inside the chunk
   int32_t s_slot[kItemQueries];                       // slot of this block in the row's id list
 };
-// B_k 64: two CTAs per CU; B_k 128: one CTA of 8 waves
-static_assert(sizeof(BwdSmem<64>) <= 80 * 1024, "LDS of a B_k 64 backward CTA");
-static_assert(sizeof(BwdSmem<128>) <= 160 * 1024, "LDS of a B_k 128 backward CTA");
+static_assert(sizeof(BwdSmem) <= 80 * 1024, "two B_k 64 backward CTAs per CU");
 
 // 256-byte rows (a pass buffer's Q / dO rows, the K block) keep their 16-byte
 // segment s in slot s ^ bwd_swz(row).  The permutation moves segment pairs
@@ -155,21 +151,21 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const uint16_t* __restri
 // reads, and dQ's B operand reads K the same way.  A pass's Q and dO rows are
 // gathered straight into LDS (DMA) one pass ahead; its dQ partials are
 // stored at the start of the next pass, so neither waits on memory.
-template <int BK>
-__global__ __launch_bounds__(bwd_threads<BK>(), BK == 64 ? 2 : 1) void bwd_kvo_kernel(
+__global__ __launch_bounds__(kBwdThreads, 2) void bwd_kvo_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, msa_seqs sq,
     const int64_t* __restrict__ blk_base, const int32_t* __restrict__ tile_off, const int32_t* __restrict__ item_off,
     const uint32_t* __restrict__ handles, int H_q, int H_kv, int topk, int64_t nbcap, int64_t row0, float scale_log2,
     uint16_t* __restrict__ dq_buf, int64_t dq_trash, float* __restrict__ part, int32_t* __restrict__ next_item) {
-  constexpr int NKW = bwd_waves<BK>();                // waves = 16-key slices of the block
-  constexpr int kThreads = bwd_threads<BK>();
+  constexpr int BK = BwdSmem::BK;
+  constexpr int NKW = kBwdWaves;                      // waves = 16-key slices of the block
+  constexpr int kThreads = kBwdThreads;
   static_assert(kItemQueries <= kThreads, "every thread loads at most one handle of an item");
   static_assert(2 * (kBwdPassRows / 4) % NKW == 0, "DMA pieces split evenly over the waves");
-  __shared__ BwdSmem<BK> sm;
+  __shared__ BwdSmem sm;
   __shared__ int32_t s_claim;
   constexpr int KS = kHeadDim / 32;                   // k-steps of S and dP over the head dimension
-  constexpr int DQU = 8 / NKW;                        // 16-dim tiles of dQ per wave
+  constexpr int DQU = 2;                              // 16-dim tiles of dQ per wave
   constexpr int kDma = 2 * (kBwdPassRows / 4) / NKW;  // 1 KiB DMA pieces per wave and pass
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
@@ -300,8 +296,7 @@ __global__ __launch_bounds__(bwd_threads<BK>(), BK == 64 ? 2 : 1) void bwd_kvo_k
         for (int i = 0; i < 4; ++i) {
           const bool odd = c16 & 1;
           uint16_t* base = dq_buf + sm.dqoff[b][16 * t + 4 * qd + i] + (kHeadDim / NKW) * kq;
-          if constexpr (DQU == 2) *reinterpret_cast<uint32_t*>(base + (odd ? 15 + c16 : c16)) = dq_pend[t][i];
-          else if (!odd) *reinterpret_cast<uint32_t*>(base + c16) = dq_pend[t][i];
+          *reinterpret_cast<uint32_t*>(base + (odd ? 15 + c16 : c16)) = dq_pend[t][i];
         }
     };
 
@@ -411,25 +406,18 @@ __global__ __launch_bounds__(bwd_threads<BK>(), BK == 64 ? 2 : 1) void bwd_kvo_k
       }
       __builtin_amdgcn_sched_barrier(0);
       // bf16 partials of the pass's rows, stored at the start of the next pass
-      // (rows without a query go to the trash row).  Two dQ tiles (4 waves):
-      // lanes c16 and c16 ^ 1 swap values so that each stores one bf16 pair
-      // (even lanes dims c16, c16 + 1 of tile 0; odd lanes dims c16 - 1, c16
-      // of tile 1).  One tile (8 waves): even lanes store dims c16, c16 + 1.
+      // (rows without a query go to the trash row): lanes c16 and c16 ^ 1 swap
+      // values so that each stores one bf16 pair (even lanes dims c16, c16 + 1
+      // of tile 0; odd lanes dims c16 - 1, c16 of tile 1)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const bool odd = c16 & 1;
-          if constexpr (DQU == 2) {
-            const float v0 = acc_q[t][0][i], v1 = acc_q[t][1][i];
-            const float mine = odd ? v1 : v0;
-            const float other = __uint_as_float(xor_lane_u32<1>(__float_as_uint(odd ? v0 : v1)));
-            dq_pend[t][i] = odd ? pack_bf16x2(other, mine) : pack_bf16x2(mine, other);
-          } else {
-            const float mine = acc_q[t][0][i];
-            const float other = __uint_as_float(xor_lane_u32<1>(__float_as_uint(mine)));
-            dq_pend[t][i] = pack_bf16x2(mine, other);
-          }
+          const float v0 = acc_q[t][0][i], v1 = acc_q[t][1][i];
+          const float mine = odd ? v1 : v0;
+          const float other = __uint_as_float(xor_lane_u32<1>(__float_as_uint(odd ? v0 : v1)));
+          dq_pend[t][i] = odd ? pack_bf16x2(other, mine) : pack_bf16x2(mine, other);
         }
       pend_buf = buf;
     }
@@ -447,6 +435,337 @@ __global__ __launch_bounds__(bwd_threads<BK>(), BK == 64 ? 2 : 1) void bwd_kvo_k
   }
 }
 
+// ---------------------------------------------------------------- 128-key blocks
+// A pass of the 64-key kernel reads its operands from LDS for every 16 keys of
+// a wave; at eight waves that is 3300 clocks of LDS reads a pass of 32 rows
+// against 1280 of MFMA.  Here a pass takes 64 rows and a wave owns 32 keys x 32
+// rows of it (kq = wave % 4, rh = wave / 4) with MFMA 32x32x16, which reads
+// each operand once per 32 keys and 32 rows: 2000 clocks of LDS reads for the
+// same work, its operands read ahead of fenced MFMA slots.  8 packed documents
+// of 745 - 3871 rows (64 heads on 4 groups, k 16): 3.40 -> 2.45 ms, 660 -> 920
+// TFLOP/s; 32768 rows: 10.0 -> 7.9 ms.  (Without the read-ahead 2.73 and 8.8 ms;
+// the registers that spill are the item loop's, none in the pass loop.)  Lane l = (n = l % 32, h = l / 32): in S = Q K^T and dP = dO V^T it
+// holds key 32kq + n and rows 8(r / 4) + 4h + r % 4 (r = 0..15), which are the
+// k-slices it supplies to dV += P^T dO and dK += dS^T Q.
+struct BwdWideSmem {
+  uint16_t k[128][kHeadDim];                          // K and V block, 256-byte rows, segments swizzled (bwd_swz)
+  uint16_t v[128][kHeadDim];
+  uint16_t qdo[2][2][64][kHeadDim];                   // Q and dO rows of a pass, double-buffered, likewise
+  uint16_t ds[64][128 + 8];                           // dS of the pass, [row][key]
+  float lse[2][64], dlt[2][64];                       // forward LSE and D per pass row (copied by DMA)
+  int32_t rpos[2][64];                                // absolute position per pass row (-1: no row)
+  int64_t dqoff[2][64];                               // element offset of the row's dQ partial (the trash row: no row)
+  int32_t s_row[kItemQueries], s_slot[kItemQueries];  // query row inside the chunk; slot of this block in its ids
+  int32_t partial[2];                                 // the pass has rows that do not see the whole block
+  int32_t claim;
+};
+static_assert(sizeof(BwdWideSmem) <= 160 * 1024, "LDS of a B_k 128 backward CTA");
+
+// Words of two consecutive rows (lo, hi) of this lane's column -> one row of
+// two adjacent columns: even lanes the first row of columns (n, n + 1), odd
+// lanes the second row of columns (n - 1, n).
+__device__ __forceinline__ uint32_t transpose_pair(uint32_t w) {
+  const uint32_t o = xor_lane_u32<1>(w);
+  return (lane_id() & 1) ? (o >> 16) | (w & 0xFFFF0000u) : (w & 0xFFFFu) | (o << 16);
+}
+
+__global__ __launch_bounds__(512) void bwd_kvo_wide_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, msa_seqs sq,
+    const int64_t* __restrict__ blk_base, const int32_t* __restrict__ tile_off, const int32_t* __restrict__ item_off,
+    const uint32_t* __restrict__ handles, int H_q, int H_kv, int topk, int64_t nbcap, int64_t row0, float scale_log2,
+    uint16_t* __restrict__ dq_buf, int64_t dq_trash, float* __restrict__ part, int32_t* __restrict__ next_item) {
+  constexpr int BK = 128;
+  constexpr int kThreads = 512;
+  constexpr int kRows = 64;                           // gathered (query, head) rows per pass
+  constexpr int kDma = 4;                             // 1 KiB DMA pieces per wave and pass
+  constexpr int KS = kHeadDim / 16;                   // k-steps of S and dP over the head dimension
+  __shared__ __align__(16) BwdWideSmem sm;
+  const int lane = lane_id();
+  const int wave = threadIdx.x / kWave;
+  const int kq = wave & 3, rh = wave >> 2;
+  const int n = lane & 31, h = lane >> 5;
+  const int G = H_q / H_kv;
+  const int qpw = kRows / G;                          // queries per pass
+  const int rows_g = qpw * G;                         // used rows of a pass
+  const int64_t ntile = static_cast<int64_t>(H_kv) * nbcap;
+  const int32_t total_items = item_off[ntile];
+  const int64_t kv_stride = static_cast<int64_t>(H_kv) * kHeadDim;
+  int64_t staged = -1;
+  const uint8_t* kbytes = reinterpret_cast<const uint8_t*>(&sm.k[0][0]);
+  // Q and dO rows come as 1 KiB pieces: piece p = 4 wave + i holds rows 4 (p %
+  // 16) .. + 3 of tensor p / 16; lane l writes slot l % 16 of row l / 16.
+  // Per piece, the query of the lane's row and its element offset (head, segment)
+  const uint16_t* dma_src = wave < 4 ? q : d_o;
+  int dma_rq[kDma], dma_el[kDma];
+#pragma unroll
+  for (int i = 0; i < kDma; ++i) {
+    const int ra = 4 * ((wave * kDma + i) & 15) + (lane >> 4);
+    dma_rq[i] = ra / G;
+    dma_el[i] = (ra % G) * kHeadDim + 8 * ((lane & 15) ^ bwd_swz(ra));
+  }
+  const int lane_rq = lane / G, lane_rh = lane % G;
+  // LDS byte offsets of the lane's operand reads.  The segment permutation is an
+  // XOR of address bits 4 - 7, so k-steps, dim tiles and row groups are reached
+  // by an XOR or an immediate from four offsets; the pass loop hides their
+  // values from the compiler, which would keep every sum in a register.
+  //   row_at   16 bytes of pass row 32rh + n (segment 2 st + h: XOR 32 st)
+  //   key_at   16 bytes of key row 32kq + n (likewise)
+  //   col_at   transposing read of pass rows 32rh + 4h + j / 4, dims 16 (l / 16
+  //            % 2) + 4 (j % 4) .., j = l % 16 (dim tile t: XOR 64 t; row + 8:
+  //            XOR 16, + 2048; row + 16: + 4096)
+  //   kcol_at  the same of key rows 8h + j / 4, dims 32kq + .. (row + 4: XOR
+  //            128, + 1024; row + 16: + 4096)
+  const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  int row_at = bwd_qrow_off(32 * rh + n, 8 * h);
+  int key_at = bwd_qrow_off(32 * kq + n, 8 * h);
+  int col_at = bwd_qrow_off(32 * rh + 4 * h + ((lane & 15) >> 2), tr_col);
+  int kcol_at = bwd_qrow_off(8 * h + ((lane & 15) >> 2), 32 * kq + tr_col);
+  const int quad_row = 32 * rh + 4 * h;               // row of accumulator registers 4g .. 4g + 3: + 8g
+  int ds_put = ((quad_row + (lane & 1)) * (BK + 8) + 32 * kq + (n & ~1)) * 2;
+  int ds_at = ((32 * rh + n) * (BK + 8) + 8 * h) * 2;
+  uint8_t* dsb = reinterpret_cast<uint8_t*>(&sm.ds[0][0]);
+
+  for (int32_t item = blockIdx.x; item < total_items; item = claim_next_item(next_item, &sm.claim)) {
+    const int64_t tile = upper_index(item_off, ntile + 1, item);
+    const int32_t h0 = tile_off[tile] + (item - item_off[tile]) * kItemQueries;
+    const int32_t nq = min(tile_off[tile + 1] - h0, kItemQueries);
+    const int r = static_cast<int>(tile / nbcap);
+    const int64_t gb = tile % nbcap;
+    const int s = static_cast<int>(upper_index(blk_base, sq.num_seqs + 1, gb));
+    const SeqGeom g = seq_geom(sq, s);
+    const int key0 = static_cast<int>(gb - blk_base[s]) * BK;
+
+    __syncthreads();                                  // the previous item is done with LDS
+    if (static_cast<int>(threadIdx.x) < nq) {
+      const uint32_t hd = handles[h0 + threadIdx.x];
+      sm.s_row[threadIdx.x] = static_cast<int32_t>(hd >> 6);
+      sm.s_slot[threadIdx.x] = static_cast<int32_t>(hd & 63u);
+    }
+    const int pos_base = g.kv_len - g.q_rows + static_cast<int>(row0 - g.q_begin);   // + row in chunk
+    if (tile != staged) {
+      const int64_t krow0 = key_blocks(sq, g, s, BK).row(key0 / BK);
+      const uint16_t* kb = k + krow0 * kv_stride + static_cast<int64_t>(r) * kHeadDim;
+      const uint16_t* vb = v + krow0 * kv_stride + static_cast<int64_t>(r) * kHeadDim;
+      for (int c = threadIdx.x; c < BK * (kHeadDim / 8); c += kThreads) {
+        const int key = c / (kHeadDim / 8), dg = c % (kHeadDim / 8);
+        const bool in = key0 + key < g.kv_len;
+        const int at = 8 * (dg ^ bwd_swz(key));
+        *reinterpret_cast<u32x4*>(&sm.k[key][at]) = in ? load_raw(kb + static_cast<int64_t>(key) * kv_stride + 8 * dg) : u32x4{};
+        *reinterpret_cast<u32x4*>(&sm.v[key][at]) = in ? load_raw(vb + static_cast<int64_t>(key) * kv_stride + 8 * dg) : u32x4{};
+      }
+      staged = tile;
+    }
+    __syncthreads();                                  // handles (and K / V) in LDS
+
+    // Q and dO rows of the pass at cc into buffer b (a row past the pass's
+    // queries reads a valid one: its P is zero)
+    const uint16_t* item_src = dma_src + static_cast<int64_t>(r) * G * kHeadDim;
+    const int64_t row_elems = static_cast<int64_t>(H_q) * kHeadDim;
+    auto issue_dma = [&](int cc, int b) {
+#pragma unroll
+      for (int i = 0; i < kDma; ++i) {
+        const int piece = wave * kDma + i;
+        const int qa = cc + dma_rq[i];
+        const int64_t grow = row0 + sm.s_row[qa < nq ? qa : min(cc, nq - 1)];
+        bwd_dma16(item_src + (grow * row_elems + dma_el[i]), &sm.qdo[b][piece >> 4][4 * (piece & 15)][0]);
+      }
+    };
+    // the pass's row scalars: wave 0 copies LSE and D into buffer b by DMA and
+    // works out positions and dQ offsets ...
+    int32_t npos = -1;
+    int64_t noff = dq_trash;
+    auto load_scalars = [&](int cc, int b) {
+      if (wave == 0) {
+        const int qa = cc + lane_rq;
+        const bool ok = lane < rows_g && qa < nq;
+        const int row = sm.s_row[ok ? qa : min(cc, nq - 1)];
+        const int64_t hr = (row0 + row) * H_q + static_cast<int64_t>(r) * G + (ok ? lane_rh : 0);
+        bwd_dma4(lse + hr, &sm.lse[b][0]);
+        bwd_dma4(delta + hr, &sm.dlt[b][0]);
+        npos = ok ? pos_base + row : -1;
+        noff = ok ? (((static_cast<int64_t>(row) * H_kv + r) * topk + sm.s_slot[qa]) * G + lane_rh) * kHeadDim : dq_trash;
+      }
+    };
+    // ... and stores those once every wave has stored the previous pass's dQ
+    // (which reads that buffer's offsets)
+    auto store_scalars = [&](int b) {
+      if (wave == 0) {
+        sm.rpos[b][lane] = npos;
+        sm.dqoff[b][lane] = noff;
+        const bool some = __ballot(npos < key0 + BK - 1) != 0;
+        if (lane == 0) sm.partial[b] = some;
+      }
+    };
+
+    f32x16 acc_dv[4], acc_dk[4];                      // [dim tile]: lane column = dim, rows = keys of the slice
+#pragma unroll
+    for (int t = 0; t < 4; ++t) { acc_dv[t] = f32x16{}; acc_dk[t] = f32x16{}; }
+    const int key = key0 + 32 * kq + n;               // this lane's key
+    // dQ values of the previous pass, stored one pass late: word j holds two
+    // dims of row 8 (j / 2) + 4h + 2 (j % 2) + (lane & 1)
+    uint32_t dq_pend[8];
+    int pend_buf = -1;
+    auto store_dq = [&](int b) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int row = quad_row + 8 * (j >> 1) + 2 * (j & 1) + (lane & 1);
+        *reinterpret_cast<uint32_t*>(dq_buf + sm.dqoff[b][row] + 32 * kq + (n & ~1)) = dq_pend[j];
+      }
+    };
+
+    issue_dma(0, 0);
+    load_scalars(0, 0);
+    store_scalars(0);
+    int buf = 0;
+    for (int c = 0; c < nq; c += qpw, buf ^= 1) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies for the pass have landed
+      __syncthreads();                                // every wave's pieces, the pass's scalars; the
+                                                      // previous pass is done with ds and the other buffer
+      if (pend_buf >= 0) store_dq(pend_buf);
+      const bool more = c + qpw < nq;
+      if (more) {
+        issue_dma(c + qpw, buf ^ 1);
+        load_scalars(c + qpw, buf ^ 1);
+      }
+      const uint8_t* qb = reinterpret_cast<const uint8_t*>(&sm.qdo[buf][0][0][0]);
+      const uint8_t* dob = qb + kRows * 2 * kHeadDim;
+      asm volatile("" : "+v"(row_at), "+v"(key_at), "+v"(col_at), "+v"(kcol_at), "+v"(ds_put), "+v"(ds_at));
+
+      // The phases below are MFMA slots, fenced so that the compiler keeps the
+      // order; operands are read one or two slots before their MFMAs.
+      // S = Q K^T, dP = dO V^T for this wave's rows and keys
+      struct Ops { bf16x8 a, b, c, d; };
+      f32x16 acc_s = f32x16{}, acc_dp = f32x16{};
+      {
+        auto read = [&](int st) -> Ops {
+          const int ro = row_at ^ (32 * st), ko = key_at ^ (32 * st);
+          return Ops{*reinterpret_cast<const bf16x8*>(qb + ro), *reinterpret_cast<const bf16x8*>(kbytes + ko),
+                     *reinterpret_cast<const bf16x8*>(dob + ro),
+                     *reinterpret_cast<const bf16x8*>(kbytes + ko + BK * 2 * kHeadDim)};
+        };
+        Ops x[KS];
+        x[0] = read(0);
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+          if (st + 1 < KS) x[st + 1] = read(st + 1);
+          acc_s = mfma32x32x16(x[st].a, x[st].b, acc_s);
+          acc_dp = mfma32x32x16(x[st].c, x[st].d, acc_dp);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (__builtin_amdgcn_readfirstlane(sm.partial[buf]) != 0) {   // rows that do not see the whole block
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          acc_s[e] = key <= sm.rpos[buf][quad_row + 8 * (e >> 2) + (e & 3)] ? acc_s[e] : -INFINITY;
+      }
+      // P and dS in place, four rows (one quad of registers) at a time
+      auto weights = [&](int g4) {
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&sm.lse[buf][quad_row + 8 * g4]);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&sm.dlt[buf][quad_row + 8 * g4]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // a row without a visible token (LSE -inf) has P = 0
+          const float l2 = l4[i] > -INFINITY ? l4[i] * kLog2e : INFINITY;
+          const float p = exp2_hw(fmaf(acc_s[4 * g4 + i], scale_log2, -l2));
+          acc_s[4 * g4 + i] = p;
+          acc_dp[4 * g4 + i] = p * (acc_dp[4 * g4 + i] - d4[i]);
+        }
+      };
+      // A operands of dV and dK (k-step u, element e = row 16u + 4h + e for e < 4,
+      // else 16u + 8 + 4h + e - 4), and dS to LDS as [row][key] for dQ
+      bf16x8 pa[2], sa[2];
+      auto pack = [&](int u) {
+        uint32_t pw[4], sw[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          pw[j] = pack_bf16x2(acc_s[8 * u + 2 * j], acc_s[8 * u + 2 * j + 1]);
+          sw[j] = pack_bf16x2(acc_dp[8 * u + 2 * j], acc_dp[8 * u + 2 * j + 1]);
+          *reinterpret_cast<uint32_t*>(dsb + ds_put + (16 * u + 8 * (j >> 1) + 2 * (j & 1)) * (BK + 8) * 2) = transpose_pair(sw[j]);
+        }
+        pa[u] = __builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
+        sa[u] = __builtin_bit_cast(bf16x8, make_uint4(sw[0], sw[1], sw[2], sw[3]));
+      };
+      // dV += P^T dO, dK += dS^T Q over the wave's 32 rows: k-step 0 of the four
+      // dim tiles, with k-step 1's weights beside it, then k-step 1
+      struct Cols { uint2 d0, d1, q0, q1; };
+      auto read_cols = [&](int j) -> Cols {
+        const int t = j & 3, u = j >> 2;
+        const int o0 = (col_at ^ (64 * t)) + 4096 * u, o1 = (col_at ^ (64 * t + 16)) + 2048 + 4096 * u;
+        return Cols{lds_tr4(dob + o0), lds_tr4(dob + o1), lds_tr4(qb + o0), lds_tr4(qb + o1)};
+      };
+      Cols y[8];
+      y[0] = read_cols(0);
+      weights(0);
+      weights(1);
+      pack(0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if (j + 1 < 8) y[j + 1] = read_cols(j + 1);
+        acc_dv[j & 3] = mfma32x32x16(pa[j >> 2], __builtin_bit_cast(bf16x8, make_uint4(y[j].d0.x, y[j].d0.y, y[j].d1.x, y[j].d1.y)), acc_dv[j & 3]);
+        acc_dk[j & 3] = mfma32x32x16(sa[j >> 2], __builtin_bit_cast(bf16x8, make_uint4(y[j].q0.x, y[j].q0.y, y[j].q1.x, y[j].q1.y)), acc_dk[j & 3]);
+        if (j == 0) weights(2);
+        if (j == 1) weights(3);
+        if (j == 2) pack(1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // dQ of the wave's 32 rows, dims 32kq + n, over the block's keys; B: keys
+      // 16ks + 8h .. + 7 of that dim, read down K's column
+      auto read_kcol = [&](int ks) -> bf16x8 {
+        const uint2 k0v = lds_tr4(kbytes + kcol_at + 4096 * ks);
+        const uint2 k1v = lds_tr4(kbytes + (kcol_at ^ 128) + 1024 + 4096 * ks);
+        return __builtin_bit_cast(bf16x8, make_uint4(k0v.x, k0v.y, k1v.x, k1v.y));
+      };
+      auto read_ds = [&](int ks) -> bf16x8 { return *reinterpret_cast<const bf16x8*>(dsb + ds_at + 32 * ks); };
+      bf16x8 kc[8], dr[8];
+      kc[0] = read_kcol(0);
+      kc[1] = read_kcol(1);
+      __syncthreads();                                // dS of every key slice in LDS; every wave's
+                                                      // store_dq of this pass has read the other buffer
+      if (more) store_scalars(buf ^ 1);               // the next pass's positions and dQ offsets
+      dr[0] = read_ds(0);
+      dr[1] = read_ds(1);
+      f32x16 acc_q = f32x16{};
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        if (ks + 2 < BK / 16) {
+          kc[ks + 2] = read_kcol(ks + 2);
+          dr[ks + 2] = read_ds(ks + 2);
+        }
+        acc_q = mfma32x32x16(dr[ks], kc[ks], acc_q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // bf16 partials of the pass's rows, stored at the start of the next pass
+      // (rows without a query go to the trash row)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dq_pend[j] = transpose_pair(pack_bf16x2(acc_q[2 * j], acc_q[2 * j + 1]));
+      pend_buf = buf;
+    }
+    if (pend_buf >= 0) store_dq(pend_buf);
+
+    // item end: the two row halves' dV and dK are added through LDS (the pass
+    // buffers: one tensor's 64 KiB) and stored as the item's partial,
+    // [tensor][kq][reg][lane]
+    float* ex = reinterpret_cast<float*>(&sm.qdo[0][0][0][0]);
+#pragma unroll
+    for (int tensor = 0; tensor < 2; ++tensor) {
+      const f32x16* acc = tensor == 0 ? acc_dv : acc_dk;
+      __syncthreads();                                // the buffers are free
+      if (rh == 1) {
+#pragma unroll
+        for (int reg = 0; reg < 64; ++reg) ex[(kq * 64 + reg) * 64 + lane] = acc[reg >> 4][reg & 15];
+      }
+      __syncthreads();
+      if (rh == 0) {
+        float* dst = part + (static_cast<int64_t>(item) * 2 + tensor) * (BK * kHeadDim) + kq * (64 * 64) + lane;
+#pragma unroll
+        for (int reg = 0; reg < 64; ++reg) dst[reg * 64] = acc[reg >> 4][reg & 15] + ex[(kq * 64 + reg) * 64 + lane];
+      }
+    }
+  }
+}
+
 // Per tile: the sum of its item partials, in item order, added to the fp32
 // accumulators of the block's keys.  bwd_reduce_split<BK>() CTAs per tile,
 // one float4 of the partial per thread, so every tile streams its partials
@@ -458,7 +777,6 @@ __global__ __launch_bounds__(256) void bwd_tile_reduce_kernel(msa_seqs sq, const
                                                               const int32_t* __restrict__ item_off, int H_kv,
                                                               int64_t nbcap, const float* __restrict__ part,
                                                               float* __restrict__ dk_acc, float* __restrict__ dv_acc) {
-  constexpr int NKW = bwd_waves<BK>();
   constexpr int kSplit = bwd_reduce_split<BK>();
   const int64_t tile = blockIdx.x / kSplit;
   const int32_t i0 = item_off[tile], i1 = item_off[tile + 1];
@@ -481,12 +799,18 @@ __global__ __launch_bounds__(256) void bwd_tile_reduce_kernel(msa_seqs sq, const
   }
   // partial layout [tensor][kq][reg][lane]: 4 consecutive lanes = 4 consecutive dims
   const int idx = 4 * c4;
-  const int tensor = idx / (NKW * 32 * 64);
-  const int kq = (idx / (32 * 64)) % NKW;
-  const int reg = (idx / 64) & 31;
+  const int tensor = idx / (BK * kHeadDim);
   const int ln = idx & 63;
-  const int key = 16 * kq + 4 * (ln >> 4) + (reg & 3);
-  const int dim = 16 * (reg >> 2) + (ln & 15);
+  int key, dim;
+  if constexpr (BK == 64) {
+    const int kq = (idx / (32 * 64)) % 4, reg = (idx / 64) & 31;
+    key = 16 * kq + 4 * (ln >> 4) + (reg & 3);
+    dim = 16 * (reg >> 2) + (ln & 15);
+  } else {
+    const int kq = (idx / (64 * 64)) % 4, reg = (idx / 64) & 63;
+    key = 32 * kq + 8 * ((reg & 15) >> 2) + 4 * (ln >> 5) + (reg & 3);
+    dim = 32 * (reg >> 4) + (ln & 31);
+  }
   if (key0 + key >= g.kv_len) return;
   float4* dst = reinterpret_cast<float4*>((tensor == 0 ? dv_acc : dk_acc) +
                                           ((key_blocks(sq, g, s, BK).row(key0 / BK) + key) * H_kv + r) *
@@ -696,6 +1020,7 @@ int run_backward(const void* q, const void* k, const void* v, const void* o, con
   const int64_t kv_floats = seqs->total_kv_rows * H_kv * static_cast<int64_t>(kHeadDim);
   const unsigned zero_blocks = static_cast<unsigned>(std::min<int64_t>((kv_floats + 255) / 256, 8192));
 
+
   msa_prof::launch("kvo_block_base_kernel", kvo_block_base_kernel, dim3(1), dim3(256), 0, stream, sq, BK, blk_base);
   msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(zero_blocks), dim3(256), 0, stream,
                    reinterpret_cast<int32_t*>(dk_acc), kv_floats, 0);
@@ -707,13 +1032,15 @@ int run_backward(const void* q, const void* k, const void* v, const void* o, con
                      dim3(256), 0, stream, static_cast<const uint16_t*>(o), static_cast<const uint16_t*>(d_o), pairs,
                      delta);
   static std::atomic<int> ctas {0};
-  const int nctas = persistent_ctas(bwd_kvo_kernel<BK>, bwd_threads<BK>(), &ctas);
+  const auto kvo = BK == 64 ? bwd_kvo_kernel : bwd_kvo_wide_kernel;
+  constexpr int threads = BK == 64 ? kBwdThreads : 512;
+  const int nctas = persistent_ctas(kvo, threads, &ctas);
   const float sl2 = softmax_scale * kLog2e;
   for (int64_t r0 = 0; r0 < seqs->total_q_rows; r0 += pl.chunk_rows) {
     const int64_t nr = std::min<int64_t>(pl.chunk_rows, seqs->total_q_rows - r0);
     build_reverse_index(block_ids, sq, blk_base, H_kv, BK, topk, pl.nbcap, pl.ntile, pl.nscan, r0, nr, cnt,
                         tile_off, item_off, blk_tot, tpos, handles, stream, true);
-    msa_prof::launch("bwd_kvo_kernel", bwd_kvo_kernel<BK>, dim3(nctas), dim3(bwd_threads<BK>()), 0, stream,
+    msa_prof::launch("bwd_kvo_kernel", kvo, dim3(nctas), dim3(threads), 0, stream,
                      static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                      static_cast<const uint16_t*>(v), static_cast<const uint16_t*>(d_o), lse,
                      static_cast<const float*>(delta), sq, static_cast<const int64_t*>(blk_base),
