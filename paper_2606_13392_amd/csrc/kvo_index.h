@@ -51,10 +51,21 @@ __device__ __forceinline__ int row_position(const msa_seqs& sq, int64_t row, int
 }
 
 // ---------------------------------------------------------------- setup
-// blk_base[s] = key blocks of the sequences before s (kv_len clamped to max_kv_len).
-__global__ __launch_bounds__(256) void kvo_block_base_kernel(msa_seqs sq, int BK, int64_t* __restrict__ blk_base) {
-  __shared__ int64_t part[256];
+// One launch: blk_base[s] = key blocks of the sequences before s (kv_len clamped
+// to max_kv_len) by the first CTA, and zeros in up to three ranges.
+struct ZeroRange {
+  int32_t* p;
+  int64_t n;
+};
+__global__ __launch_bounds__(256) void kvo_setup_kernel(msa_seqs sq, int BK, int64_t* __restrict__ blk_base,
+                                                        ZeroRange z0, ZeroRange z1, ZeroRange z2) {
   const int t = threadIdx.x;
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * 256 + t, step = static_cast<int64_t>(gridDim.x) * 256;
+  for (int64_t i = first; i < z0.n; i += step) z0.p[i] = 0;
+  for (int64_t i = first; i < z1.n; i += step) z1.p[i] = 0;
+  for (int64_t i = first; i < z2.n; i += step) z2.p[i] = 0;
+  if (blockIdx.x != 0) return;
+  __shared__ int64_t part[256];
   const int S = sq.num_seqs;
   const int per = (S + 255) / 256;
   const int s0 = t * per, s1 = min(S, s0 + per);
@@ -76,6 +87,12 @@ __global__ __launch_bounds__(256) void kvo_block_base_kernel(msa_seqs sq, int BK
   acc = part[t];
   for (int s = s0; s < s1; ++s) { blk_base[s] = acc; acc += nblk(s); }
 }
+inline void launch_setup(const msa_seqs& sq, int BK, int64_t* blk_base, hipStream_t stream, ZeroRange z0,
+                         ZeroRange z1 = {nullptr, 0}, ZeroRange z2 = {nullptr, 0}) {
+  const int64_t most = std::max(std::max(z0.n, z1.n), std::max<int64_t>(z2.n, 1));
+  msa_prof::launch("kvo_setup_kernel", kvo_setup_kernel, dim3(static_cast<unsigned>(std::min<int64_t>((most + 255) / 256, 8192))),
+                   dim3(256), 0, stream, sq, BK, blk_base, z0, z1, z2);
+}
 
 __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
@@ -85,27 +102,27 @@ __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, 
 
 // ---------------------------------------------------------------- reverse index
 // Positions of every incidence inside its tile's handle list, with few device
-// atomics: a CTA takes kHistRows query rows of one group, histograms their
+// atomics: a CTA takes hist_rows query rows of one group, histograms their
 // incidences over the key blocks of its sequences in LDS, claims one segment
 // of each touched tile with a single device atomic (the returned count is the
 // segment's start) and hands out positions inside its segments with LDS
 // atomics.  A CTA whose sequences span more than kHistBins key blocks falls
 // back to one device atomic per incidence.  Positions are relative to the
 // tile; kvo_fill adds the tile offsets once the scan has run.  1024 rows per
-// CTA: a 32K-row chunk of 8 groups gives 256 CTAs (with 4096 rows, 64 CTAs
-// left most CUs idle and the kernel took 3.5x as long).
-constexpr int kHistRows = 1024;
+// CTA where that gives 256 CTAs, down to 256 rows for smaller chunks (17380
+// rows of 4 groups: 72 CTAs and 41 us against 288 and 22).
+constexpr int kHistRows = 1024, kMinHistRows = 256, kHistCtas = 256;
 constexpr int kHistBins = 16384;
 
 __global__ __launch_bounds__(256) void kvo_count_kernel(const int32_t* __restrict__ block_ids, msa_seqs sq,
                                                         const int64_t* __restrict__ blk_base, int H_kv, int BK,
                                                         int topk, int64_t nbcap, int64_t row0, int64_t nrows,
-                                                        int p_min, int32_t* __restrict__ cnt,
+                                                        int hist_rows, int p_min, int32_t* __restrict__ cnt,
                                                         int32_t* __restrict__ tpos) {
   __shared__ int32_t hist[kHistBins];
   const int r = blockIdx.y;
-  const int64_t rb0 = row0 + static_cast<int64_t>(blockIdx.x) * kHistRows;
-  const int64_t rb1 = min(rb0 + kHistRows, row0 + nrows);
+  const int64_t rb0 = row0 + static_cast<int64_t>(blockIdx.x) * hist_rows;
+  const int64_t rb1 = min(rb0 + hist_rows, row0 + nrows);
   const int s_first = find_seq_wave(sq.q_offsets, sq.num_seqs, rb0);
   const int s_last = find_seq_wave(sq.q_offsets, sq.num_seqs, rb1 - 1);
   const int64_t g_lo = blk_base[s_first];
@@ -114,7 +131,7 @@ __global__ __launch_bounds__(256) void kvo_count_kernel(const int32_t* __restric
   const int64_t tile_base = static_cast<int64_t>(r) * nbcap;
 
   if (in_lds) {
-    for (int i = threadIdx.x; i < kHistBins; i += 256) hist[i] = 0;
+    for (int i = threadIdx.x; i < static_cast<int>(g_hi - g_lo); i += 256) hist[i] = 0;
     __syncthreads();
   }
   // pass 1: histogram (or, without LDS room, claim each position directly);
@@ -212,8 +229,42 @@ __global__ __launch_bounds__(256) void kvo_fill_kernel(const int32_t* __restrict
   }
 }
 
-// Two-array exclusive scan (handles per tile, work items per tile) in three
-// kernels: per-block scan, scan of block totals, add.
+// Two-array exclusive scan (handles per tile, work items per tile): one CTA for
+// up to kScanOne tiles, else three kernels (per-block scan, scan of block
+// totals, add).
+constexpr int kScanOne = 16384;       // 1024 threads x 16
+__global__ __launch_bounds__(1024) void kvo_scan_one_kernel(const int32_t* __restrict__ cnt, int n,
+                                                            int32_t* __restrict__ tile_off,
+                                                            int32_t* __restrict__ item_off) {
+  __shared__ int32_t wa[1024 / kWave], wb[1024 / kWave];
+  const int t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+  const int per = (n + 1023) / 1024;
+  const int i0 = min(n, t * per), i1 = min(n, i0 + per);
+  int32_t ta = 0, tb = 0;
+  for (int i = i0; i < i1; ++i) {
+    const int32_t c = cnt[i];
+    ta += c;
+    tb += (c + kItemQueries - 1) / kItemQueries;
+  }
+  // sums of the threads before this one: within the wave, then over the waves
+  int32_t a = ta, b = tb;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t xa = __shfl_up(a, off), xb = __shfl_up(b, off);
+    if (lane >= off) { a += xa; b += xb; }
+  }
+  if (lane == kWave - 1) { wa[wave] = a; wb[wave] = b; }
+  __syncthreads();
+  int32_t pa = a - ta, pb = b - tb;
+  for (int w = 0; w < wave; ++w) { pa += wa[w]; pb += wb[w]; }
+  for (int i = i0; i < i1; ++i) {
+    tile_off[i] = pa;
+    item_off[i] = pb;
+    const int32_t c = cnt[i];
+    pa += c;
+    pb += (c + kItemQueries - 1) / kItemQueries;
+  }
+  if (t == 1023) { tile_off[n] = pa; item_off[n] = pb; }
+}
 constexpr int kScanPerBlock = 2048;   // 256 threads x 8
 
 __global__ __launch_bounds__(256) void kvo_scan_block_kernel(const int32_t* __restrict__ cnt, int64_t n,
@@ -314,21 +365,6 @@ int persistent_ctas(K kernel, int threads, std::atomic<int>* cache) {
   }
   return n;
 }
-// Block ids of B_k = 64 f from ids of blocks of 64 f keys: block b becomes its
-// f sub-blocks f b .. f b + f - 1 (ascending order and -1 padding kept), so a
-// 64-key kernel covers exactly the same tokens.  One thread per (row, group).
-__global__ __launch_bounds__(256) void expand_block_ids_kernel(const int32_t* __restrict__ ids, int64_t pairs,
-                                                               int topk, int f, int32_t* __restrict__ out) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= pairs) return;
-  const int32_t* src = ids + i * topk;
-  int32_t* dst = out + i * topk * f;
-  for (int j = 0; j < topk; ++j) {
-    const int32_t b = src[j];
-    for (int e = 0; e < f; ++e) dst[j * f + e] = b >= 0 ? b * f + e : -1;
-  }
-}
-
 // Persistent work loops: a CTA's first item is blockIdx.x, later ones are
 // claimed from a global counter, so CTAs that drew cheap items take more
 // (the dynamic load balancing of Sec. 4.3).  The counters sit after the
@@ -350,7 +386,9 @@ __device__ __forceinline__ int32_t claim_next_item(int32_t* __restrict__ next_it
 // sort each list into ascending handle order -- row, then slot -- which makes
 // their results bit-reproducible.  A row selects a block once, so a tile's
 // handles have distinct rows and the order is the rows' order.  One CTA per
-// tile, two launches:
+// tile; sequences of at most kSpanRows query rows take one launch:
+//   order_tile_handles_kernel  every tile by a bitmap over the sequence's rows
+// and longer ones two:
 //   sort_tile_handles_kernel   tiles of at most kSortRun handles: bitonic
 //                              sort in LDS;
 //   rank_tile_handles_kernel   longer tiles: the rows are marked in an LDS
@@ -524,6 +562,90 @@ __global__ __launch_bounds__(256) void rank_tile_handles_kernel(uint32_t* __rest
   for (int32_t i = tid; i < n; i += 256) a[i] = b[i];
 }
 
+// The same order where every sequence has at most kSpanRows query rows, so that
+// a bitmap over one sequence's rows takes 8 KiB and many CTAs share a CU:
+// handles of 8 documents of up to 3871 rows 98 us (two launches, bitonic sorts
+// for the short lists) -> 18.
+constexpr int kSpanRows = 65536;
+constexpr int kSpanWords = kSpanRows / 32;
+static_assert(kSpanWords >= kSortRun, "the bitmap doubles as the sort buffer");
+
+__global__ __launch_bounds__(256) void order_tile_handles_kernel(uint32_t* __restrict__ handles,
+                                                                 uint32_t* __restrict__ tmp, msa_seqs sq,
+                                                                 const int64_t* __restrict__ blk_base, int64_t nbcap,
+                                                                 int64_t row0, int64_t nrows,
+                                                                 const int32_t* __restrict__ tile_off) {
+  __shared__ uint32_t map[kSpanWords];
+  __shared__ int32_t before[kSpanWords];              // marked rows before each word
+  __shared__ int32_t sums[256 / kWave];
+  const int64_t t = blockIdx.x;
+  const int32_t beg = tile_off[t];
+  const int32_t n = tile_off[t + 1] - beg;
+  if (n <= 1) return;                                 // uniform over the CTA
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  uint32_t* a = handles + beg;
+  uint32_t* b = tmp + beg;
+  // the chunk's rows of the tile's sequence: first .. first + span - 1
+  const int s = static_cast<int>(upper_index(blk_base, sq.num_seqs + 1, t % nbcap));
+  const int64_t q0 = static_cast<int64_t>(sq.q_offsets[s]) - row0, q1 = static_cast<int64_t>(sq.q_offsets[s + 1]) - row0;
+  const int32_t first = static_cast<int32_t>(q0 > 0 ? q0 : 0);
+  const int64_t span = min(q1, nrows) - first;
+  const int nw = static_cast<int>(min(span + 31, static_cast<int64_t>(kSpanRows)) / 32);
+  const int per = (nw + 255) / 256;                   // consecutive words per thread, at most 8
+  for (int i = tid; i < nw; i += 256) map[i] = 0;
+  __syncthreads();
+  for (int32_t i = tid; i < n; i += 256) {
+    const uint32_t r = (a[i] >> 6) - first;
+    if (r < static_cast<uint32_t>(32 * nw)) atomicOr(&map[r >> 5], 1u << (r & 31));
+  }
+  __syncthreads();
+  int32_t own = 0;
+  for (int w = tid * per; w < min(nw, tid * per + per); ++w) own += __popc(map[w]);
+  int32_t run = own;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t x = __shfl_up(run, off);
+    if (lane >= off) run += x;
+  }
+  if (lane == kWave - 1) sums[wave] = run;
+  __syncthreads();
+  int32_t total = 0, base = run - own;
+#pragma unroll
+  for (int w = 0; w < 256 / kWave; ++w) {
+    base += w < wave ? sums[w] : 0;
+    total += sums[w];
+  }
+  if (total != n) {                                   // a row listed twice (not a valid selection):
+    __syncthreads();                                  // order by (row, slot) all the same
+    sort_by_merging(a, b, n, map);
+    return;
+  }
+  for (int w = tid * per; w < min(nw, tid * per + per); ++w) {
+    before[w] = base;
+    base += __popc(map[w]);
+  }
+  __syncthreads();
+  auto place = [&](uint32_t hd) -> int32_t {
+    const uint32_t r = (hd >> 6) - first;
+    return before[r >> 5] + __popc(map[r >> 5] & ((1u << (r & 31)) - 1u));
+  };
+  if (n <= 4 * 256) {                                 // short lists stay in registers between read and write
+    uint32_t hd[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) hd[e] = tid + 256 * e < n ? a[tid + 256 * e] : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (tid + 256 * e < n) a[place(hd[e])] = hd[e];
+    return;
+  }
+  for (int32_t i = tid; i < n; i += 256) {
+    const uint32_t hd = a[i];
+    b[place(hd)] = hd;
+  }
+  __syncthreads();
+  for (int32_t i = tid; i < n; i += 256) a[i] = b[i];
+}
+
 // Reverse index of query rows r0 .. r0 + nr - 1 (one chunk): counts, scans
 // and handle lists for every tile of H_kv x nbcap; `canonical` sorts each
 // list.  Rows at positions below p_min stay out of it.
@@ -531,29 +653,43 @@ void build_reverse_index(const int32_t* block_ids, const msa_seqs& sq, const int
                          int topk, int64_t nbcap, int64_t ntile, int nscan, int64_t r0, int64_t nr, int32_t* cnt,
                          int32_t* tile_off, int32_t* item_off, int32_t* blk_tot, int32_t* tpos, uint32_t* handles,
                          hipStream_t stream, bool canonical = false, int p_min = INT32_MIN) {
-  const unsigned fill_blocks = static_cast<unsigned>(std::min<int64_t>((ntile + kWorkCounters + 255) / 256, 4096));
   const unsigned gthreads = static_cast<unsigned>((nr * H_kv + 256 / kWave - 1) / (256 / kWave));   // a wave per pair
-  msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, cnt,
-                   ntile + kWorkCounters, 0);
-  const dim3 hgrid(static_cast<unsigned>((nr + kHistRows - 1) / kHistRows), static_cast<unsigned>(H_kv));
+  // the first chunk's counters are cleared by the call's setup launch
+  if (r0 > 0)
+    msa_prof::launch("fill_i32_kernel", fill_i32_kernel,
+                     dim3(static_cast<unsigned>(std::min<int64_t>((ntile + kWorkCounters + 255) / 256, 4096))),
+                     dim3(256), 0, stream, cnt, ntile + kWorkCounters, 0);
+  int hist_rows = kHistRows;
+  while (hist_rows > kMinHistRows && (nr + hist_rows - 1) / hist_rows * H_kv < kHistCtas) hist_rows /= 2;
+  const dim3 hgrid(static_cast<unsigned>((nr + hist_rows - 1) / hist_rows), static_cast<unsigned>(H_kv));
   msa_prof::launch("kvo_count_kernel", kvo_count_kernel, hgrid, dim3(256), 0, stream, block_ids, sq, blk_base, H_kv,
-                   BK, topk, nbcap, r0, nr, p_min, cnt, tpos);
-  msa_prof::launch("kvo_scan_block_kernel", kvo_scan_block_kernel, dim3(nscan), dim3(256), 0, stream, cnt, ntile,
-                   tile_off, item_off, blk_tot);
-  msa_prof::launch("kvo_scan_top_kernel", kvo_scan_top_kernel, dim3(1), dim3(1024), 0, stream, blk_tot, nscan,
-                   tile_off, item_off, ntile);
-  msa_prof::launch("kvo_scan_add_kernel", kvo_scan_add_kernel, dim3(static_cast<unsigned>((ntile + 255) / 256)),
-                   dim3(256), 0, stream, blk_tot, ntile, tile_off, item_off);
+                   BK, topk, nbcap, r0, nr, hist_rows, p_min, cnt, tpos);
+  if (ntile <= kScanOne) {
+    msa_prof::launch("kvo_scan_one_kernel", kvo_scan_one_kernel, dim3(1), dim3(1024), 0, stream, cnt,
+                     static_cast<int>(ntile), tile_off, item_off);
+  } else {
+    msa_prof::launch("kvo_scan_block_kernel", kvo_scan_block_kernel, dim3(nscan), dim3(256), 0, stream, cnt, ntile,
+                     tile_off, item_off, blk_tot);
+    msa_prof::launch("kvo_scan_top_kernel", kvo_scan_top_kernel, dim3(1), dim3(1024), 0, stream, blk_tot, nscan,
+                     tile_off, item_off, ntile);
+    msa_prof::launch("kvo_scan_add_kernel", kvo_scan_add_kernel, dim3(static_cast<unsigned>((ntile + 255) / 256)),
+                     dim3(256), 0, stream, blk_tot, ntile, tile_off, item_off);
+  }
   msa_prof::launch("kvo_fill_kernel", kvo_fill_kernel, dim3(gthreads), dim3(256), 0, stream, block_ids, sq, blk_base,
                    H_kv, BK, topk, nbcap, r0, nr, p_min, tile_off, tpos, handles);
+  if (!canonical) return;
   // positions are no longer needed: tpos is the long tiles' scatter buffer
-  if (canonical) {
-    msa_prof::launch("sort_tile_handles_kernel", sort_tile_handles_kernel, dim3(static_cast<unsigned>(ntile)),
-                     dim3(256), 0, stream, handles, static_cast<const int32_t*>(tile_off));
-    msa_prof::launch("rank_tile_handles_kernel", rank_tile_handles_kernel, dim3(static_cast<unsigned>(ntile)),
-                     dim3(256), 0, stream, handles, reinterpret_cast<uint32_t*>(tpos),
+  if (sq.max_q_rows <= kSpanRows) {
+    msa_prof::launch("order_tile_handles_kernel", order_tile_handles_kernel, dim3(static_cast<unsigned>(ntile)),
+                     dim3(256), 0, stream, handles, reinterpret_cast<uint32_t*>(tpos), sq, blk_base, nbcap, r0, nr,
                      static_cast<const int32_t*>(tile_off));
+    return;
   }
+  msa_prof::launch("sort_tile_handles_kernel", sort_tile_handles_kernel, dim3(static_cast<unsigned>(ntile)),
+                   dim3(256), 0, stream, handles, static_cast<const int32_t*>(tile_off));
+  msa_prof::launch("rank_tile_handles_kernel", rank_tile_handles_kernel, dim3(static_cast<unsigned>(ntile)),
+                   dim3(256), 0, stream, handles, reinterpret_cast<uint32_t*>(tpos),
+                   static_cast<const int32_t*>(tile_off));
 }
 
 }  // namespace

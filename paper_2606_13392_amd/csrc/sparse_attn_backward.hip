@@ -1020,12 +1020,8 @@ int run_backward(const void* q, const void* k, const void* v, const void* o, con
   const int64_t kv_floats = seqs->total_kv_rows * H_kv * static_cast<int64_t>(kHeadDim);
   const unsigned zero_blocks = static_cast<unsigned>(std::min<int64_t>((kv_floats + 255) / 256, 8192));
 
-
-  msa_prof::launch("kvo_block_base_kernel", kvo_block_base_kernel, dim3(1), dim3(256), 0, stream, sq, BK, blk_base);
-  msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(zero_blocks), dim3(256), 0, stream,
-                   reinterpret_cast<int32_t*>(dk_acc), kv_floats, 0);
-  msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(zero_blocks), dim3(256), 0, stream,
-                   reinterpret_cast<int32_t*>(dv_acc), kv_floats, 0);
+  launch_setup(sq, BK, blk_base, stream, {reinterpret_cast<int32_t*>(dk_acc), kv_floats},
+               {reinterpret_cast<int32_t*>(dv_acc), kv_floats}, {cnt, pl.ntile + kWorkCounters});
   const int64_t pairs = seqs->total_q_rows * H_q;
   if (pairs > 0)
     msa_prof::launch("bwd_delta_kernel", bwd_delta_kernel, dim3(static_cast<unsigned>((pairs * 16 + 255) / 256)),

@@ -577,7 +577,7 @@ int msa_kvo_prefill(const void* q, const void* k, const void* v, const int32_t* 
     if (st != MSA_OK || seqs->max_kv_len <= p_cut) return st != MSA_OK ? st : msa_host::launch_status();
   }
   const int p_min = p_cut > 0 ? p_cut : INT32_MIN;
-  msa_prof::launch("kvo_block_base_kernel", kvo_block_base_kernel, dim3(1), dim3(256), 0, stream, sq, BK, blk_base);
+  launch_setup(sq, BK, blk_base, stream, {cnt, pl.ntile + kWorkCounters});
   for (int64_t r0 = 0; r0 < seqs->total_q_rows; r0 += pl.chunk_rows) {
     const int64_t nr = std::min<int64_t>(pl.chunk_rows, seqs->total_q_rows - r0);
     build_reverse_index(block_ids, sq, blk_base, H_kv, BK, topk, pl.nbcap, pl.ntile, pl.nscan, r0, nr, cnt, tile_off,

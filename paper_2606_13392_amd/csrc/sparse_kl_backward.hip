@@ -148,8 +148,10 @@ __global__ __launch_bounds__(kKlThreads) void kl_lse_kernel(
 constexpr int kLseCombWaves = 4;
 __global__ __launch_bounds__(64 * kLseCombWaves) void kl_lse_combine_kernel(
     const int32_t* __restrict__ block_ids, msa_seqs sq, const int64_t* __restrict__ blk_base, int BK, int H_kv,
-    int topk, int64_t row0, int64_t nrows, const float* __restrict__ lse_part, float* __restrict__ lse_idx) {
+    int topk, int64_t row0, int64_t nrows, const float* __restrict__ lse_part, float* __restrict__ lse_idx,
+    int32_t* __restrict__ next_item) {
   const int lane = lane_id();
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next_item = 0;   // the sweep's work counter, for the next persistent loop
   const int64_t pr = static_cast<int64_t>(blockIdx.x) * kLseCombWaves + threadIdx.x / kWave;
   if (pr >= nrows * H_kv) return;
   const int64_t row = row0 + pr / H_kv;
@@ -810,13 +812,10 @@ int run_kl(const void* index_q, const void* index_k, const void* q, const void* 
   const auto* ik = static_cast<const uint16_t*>(index_k);
   const int64_t trash_inc = pl.chunk_rows * H_kv * static_cast<int64_t>(topk);
 
-  msa_prof::launch("kvo_block_base_kernel", kvo_block_base_kernel, dim3(1), dim3(256), 0, stream, sq, BK,
-                   blk_base);
-  msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(zero_blocks), dim3(256), 0, stream,
-                   reinterpret_cast<int32_t*>(dk_acc), kv_floats, 0);
-  // the trash incidence's Delta row stands in for the query slots past an item: zero
-  msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(1), dim3(256), 0, stream,
-                   reinterpret_cast<int32_t*>(dlt + trash_inc * BK), static_cast<int64_t>(BK / 2), 0);
+  // (the trash incidence's Delta row stands in for the query slots past an item: zero)
+  launch_setup(sq, BK, blk_base, stream, {reinterpret_cast<int32_t*>(dk_acc), kv_floats},
+               {reinterpret_cast<int32_t*>(dlt + trash_inc * BK), static_cast<int64_t>(BK / 2)},
+               {cnt, pl.ntile + kWorkCounters});
   static std::atomic<int> ctas_lse {0}, ctas_grad {0}, ctas_dk {0};
   const int n_lse = persistent_ctas(kl_lse_kernel<BK, D>, kKlThreads, &ctas_lse);
   const int n_grad = persistent_ctas(kl_grad_kernel<BK, D, 3>, kK2Threads, &ctas_grad);
@@ -834,16 +833,14 @@ int run_kl(const void* index_q, const void* index_k, const void* q, const void* 
     msa_prof::launch("kl_lse_combine_kernel", kl_lse_combine_kernel,
                      dim3(static_cast<unsigned>((pairs + kLseCombWaves - 1) / kLseCombWaves)),
                      dim3(64 * kLseCombWaves), 0, stream, block_ids, sq, static_cast<const int64_t*>(blk_base), BK, H_kv, topk, r0,
-                     nr, static_cast<const float*>(lsep), lsei);
+                     nr, static_cast<const float*>(lsep), lsei, cnt + pl.ntile);
     launch_kl_grad<BK, D>(lg_g, dim3(n_grad), stream, iq, ik, static_cast<const uint16_t*>(q),
                           static_cast<const uint16_t*>(k), lse, static_cast<const float*>(lsei), sq,
                           static_cast<const int64_t*>(blk_base), static_cast<const int32_t*>(tile_off),
                           static_cast<const int32_t*>(item_off), static_cast<const uint32_t*>(handles), H_q, H_kv,
                           topk, pl.nbcap, r0, softmax_scale * kLog2e, sidx * kLog2e, trash_inc, dqp, klp, dlt,
                           cnt + pl.ntile + 1);
-    // d k_idx's persistent loop reuses the LSE sweep's work counter, reset
-    msa_prof::launch("fill_i32_kernel", fill_i32_kernel, dim3(1), dim3(256), 0, stream, cnt + pl.ntile,
-                     static_cast<int64_t>(1), 0);
+    // (d k_idx's persistent loop reuses the LSE sweep's work counter)
     msa_prof::launch("kl_dk_kernel", kl_dk_kernel<BK, D>, dim3(n_dk), dim3(kK2Threads), 0, stream, iq, sq,
                      static_cast<const int64_t*>(blk_base), static_cast<const int32_t*>(tile_off),
                      static_cast<const int32_t*>(item_off), static_cast<const uint32_t*>(handles), H_kv, topk,

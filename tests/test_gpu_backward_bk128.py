@@ -29,3 +29,14 @@ def test_backward_bk128(case):
     ids[::17] = -1
     got = list(_run(p, x, ids))
     _check_all(case[0], got, O.sparse_attention_backward(x["q"], x["k"], x["v"], x["d_o"], ids, O.layout_of(p), p.block_size))
+
+
+@pytest.mark.parametrize("rows", [1, 2, 63, 1023, 1024, 1025, 2500])
+def test_backward_reproducible_list_lengths(rows):
+    """Block 0 is listed by every row: handle lists of `rows` entries, ordered
+    in registers up to 1024 and through the scratch list beyond.  dK and dV add
+    a list in its order, so three runs agree bit for bit."""
+    p, x, ids = _setup(f"bwd_list_{rows}", [rows, 70], [rows, 70], 8, 2, 40, None, 64)
+    first, *rest = (list(_run(p, x, ids)) for _ in range(3))
+    for r in rest:
+        assert all((a == b).all() for a, b in zip(first, r))
