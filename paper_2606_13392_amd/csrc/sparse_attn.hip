@@ -12,6 +12,15 @@
 // their states through LDS with the log-sum-exp rule of Sec. 4.2 ("Two-phase
 // forward").  With several splits per row the CTA writes a locally normalised
 // partial that combine_kernel merges by the same rule.
+//
+// Keys are taken 64 at a time whatever the block size: a 128-key block is two
+// slots.  (A kernel of its own for 128-key blocks held one CTA of 4 waves per
+// CU, 136 KB of LDS, and loaded E4M3 keys 8 bytes per lane: 51 us for 16
+// sequences x 4 rows at 60K, k 16, paged, against 37; 64 sequences at 128K
+// 50 -> 38 us E4M3, 62 -> 53 us bf16.)
+// Large steps are bound by the cache's bytes: 64 sequences at 128K, 8 groups,
+// k 32 of 64-key blocks in bf16 (537 MB) take 99 us, 5.4 TB/s.  Small ones by
+// the chain ids -> keys -> softmax -> merge: one row at 8K 17.2 -> 11.8 us.
 #include "msa_common.h"
 #include "msa_profile.h"
 
@@ -28,21 +37,22 @@ constexpr int kRedStride = kHeadDim + 4;      // fp32 row stride of the merge bu
 
 constexpr int kKRowPad = kHeadDim + 8;       // bf16 K rows staged with 16 bytes of padding
 
-template <int BK>
+constexpr int kSub = 64;                      // keys per slot
+
 struct AttnSmem {
-  union {                                        // kr: 64-key bf16 blocks only
-    // bf16 K of one block, row-major kr[key][d]: the rows arrive as whole
+  union {
+    // bf16 K of one slot, row-major kr[key][d]: the rows arrive as whole
     // 256-byte rows (16 lanes per row) and are read back as MFMA operands
-    uint16_t kr[BK == 64 ? BK : 1][kKRowPad];
-    // E4M3 K of one 64-key block, row-major kr8[key][d] (+16 B pad per row)
-    uint8_t kr8[BK == 64 ? BK : 1][kHeadDim + 16];
-    // V of one block, transposed: vt[d][key]; +4 keys of padding per row.
-    // After the block loop the same bytes hold the wave's scaled O (16 x
+    uint16_t kr[kSub][kKRowPad];
+    // E4M3 K, row-major kr8[key][d] (+16 B pad per row)
+    uint8_t kr8[kSub][kHeadDim + 16];
+    // V, transposed: vt[d][key]; +4 keys of padding per row.
+    // After the slot loop the same bytes hold the wave's scaled O (16 x
     // kRedStride fp32).
-    uint16_t vt[kHeadDim][BK + 4];
+    uint16_t vt[kHeadDim][kSub + 4];
   };
 };
-static_assert(sizeof(AttnSmem<64>) >= 16 * kRedStride * sizeof(float), "merge buffer does not fit");
+static_assert(sizeof(AttnSmem) >= 16 * kRedStride * sizeof(float), "merge buffer does not fit");
 
 // Orders a wave's own LDS accesses (a wave's LDS operations complete in issue
 // order; this keeps the compiler from moving them across).
@@ -51,29 +61,13 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// V[b*BK .. b*BK+BK) of group r: each lane loads 4 keys x 8 dims per
-// (4-key group, 8-dim group) pair; keys past the sequence's end read as zero.
-template <int BK, typename T>
-__device__ __forceinline__ void load_v_raw(const T* __restrict__ vbase, int64_t row_stride, int key0,
-                                           int kv_len, Raw<T> (&raw)[BK / 16][4]) {
+// Raw V of one slot, 4 keys x 8 dims per lane and (4-key group, 8-dim group)
+// pair, widened to bf16 and transposed into LDS as vt[d][key].
+template <typename R>
+__device__ __forceinline__ void store_v_transposed(AttnSmem& sm, const R (&raw_in)[kSub / 16][4]) {
   const int lane = lane_id();
 #pragma unroll
-  for (int it = 0; it < BK / 16; ++it) {
-    const int q = lane + kWave * it;        // (4-key group, 8-dim group)
-    const int key4 = q >> 4, dg = q & 15;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int key = key0 + 4 * key4 + j;
-      raw[it][j] = key < kv_len ? load_raw(vbase + static_cast<int64_t>(key) * row_stride + 8 * dg) : Raw<T>{};
-    }
-  }
-}
-// ... and stores them (widened to bf16) transposed into LDS as vt[d][key].
-template <int BK, typename R>
-__device__ __forceinline__ void store_v_transposed(AttnSmem<BK>& sm, const R (&raw_in)[BK / 16][4]) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int it = 0; it < BK / 16; ++it) {
+  for (int it = 0; it < kSub / 16; ++it) {
     const int q = lane + kWave * it;
     const int key4 = q >> 4, dg = q & 15;
     u32x4 raw[1][4];
@@ -92,25 +86,38 @@ __device__ __forceinline__ void store_v_transposed(AttnSmem<BK>& sm, const R (&r
 
 // T: element type of Q, K and V (uint16_t = bf16 bits, uint8_t = e4m3 bits);
 // o_scale multiplies O (the V dequantisation scale for e4m3).
-template <int BK, typename T, bool PAGED>
-// (64-key bf16 blocks on a contiguous cache fit 2 CTAs per CU in 256
-// registers: 108 -> 106 us per 128K step against one wave per SIMD.)
-__global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PAGED) ? 2 : 1) void attn_rows_kernel(
+// A row's slots are topk << sub_shift: slot s is keys 64 (s % 2^sub_shift) ..
+// of its block id s >> sub_shift.
+template <typename T, bool PAGED>
+// two CTAs per CU in 256 registers: bf16 on a contiguous cache 108 -> 106 us
+// per 128K step against one wave per SIMD
+__global__ __launch_bounds__(64 * kAttnWaves, 2) void attn_rows_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ block_ids, msa_seqs sq, int H_q, int H_kv, int topk,
-    int slots_per_wave, float scale_log2, float o_scale, uint16_t* __restrict__ o, float* __restrict__ lse,
+    int sub_shift, int slots_per_wave, float scale_log2, float o_scale, uint16_t* __restrict__ o, float* __restrict__ lse,
     float* __restrict__ o_part, float* __restrict__ lse_part) {
-  __shared__ __align__(16) AttnSmem<BK> smw[kAttnWaves];
+  __shared__ __align__(16) AttnSmem smw[kAttnWaves];
   __shared__ float mls[kAttnWaves][2][16];
   const int lane = lane_id();
   const int wv = threadIdx.x / kWave;
-  AttnSmem<BK>& sm = smw[wv];
+  AttnSmem& sm = smw[wv];
   const int G = H_q / H_kv;
   const int64_t row = blockIdx.x / H_kv;
   const int r = blockIdx.x % H_kv;
   const int sp = blockIdx.y;
   const int nsplit = gridDim.y;
   if (row >= sq.total_q_rows) return;                // uniform over the CTA
+  // the wave's slots, one per lane, fetched at once (slots_per_wave <= 64 with
+  // ids); without block ids (dense mode) slot b is key block b
+  const int nslots = topk << sub_shift;
+  const int slot0 = min(nslots, (sp * kAttnWaves + wv) * slots_per_wave);
+  const int slot1 = min(nslots, slot0 + slots_per_wave);
+  const int32_t* ids = block_ids ? block_ids + (row * H_kv + r) * topk : nullptr;
+  int my_b = -1;
+  if (ids && slot0 + lane < slot1) {
+    const int id = ids[(slot0 + lane) >> sub_shift];
+    my_b = id < 0 ? -1 : (id << sub_shift) + ((slot0 + lane) & ((1 << sub_shift) - 1));
+  }
   const int s = find_seq_wave(sq.q_offsets, sq.num_seqs, row);
   const SeqGeom g = seq_geom(sq, s);
   int p = g.kv_len - g.q_rows + static_cast<int>(row - g.q_begin);
@@ -124,92 +131,107 @@ __global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PA
   for (int ks = 0; ks < kHeadDim / 32; ++ks) bq[ks] = widen_bf16x8(n < G ? load_raw(qrow + 32 * ks) : Raw<T>{});
 
   const int64_t kv_stride = static_cast<int64_t>(H_kv) * kHeadDim;
-  const KeyBlocks kbk = key_blocks(sq, g, s, BK);
+  const KeyBlocks kbk = key_blocks(sq, g, s, kSub);   // 64-key view of the blocks
   const int64_t seq0 = PAGED ? 0 : g.kv_start;           // contiguous: keys from kv_start
-  const T* kbase = k + seq0 * kv_stride + static_cast<int64_t>(r) * kHeadDim + 8 * q4;
-  const T* krow_base = k + seq0 * kv_stride + static_cast<int64_t>(r) * kHeadDim;   // row starts
+  const T* kbase = k + seq0 * kv_stride + static_cast<int64_t>(r) * kHeadDim;   // row starts
   const T* vbase = v + seq0 * kv_stride + static_cast<int64_t>(r) * kHeadDim;
-  // without block ids (dense mode) slot b is key block b
-  const int32_t* ids = block_ids ? block_ids + (row * H_kv + r) * topk : nullptr;
+  // the lane's part of the K and V addresses within a slot
+  const int koff = sizeof(T) == 1 ? (lane >> 3) * static_cast<int>(kv_stride) + 16 * (lane & 7)
+                                  : q4 * static_cast<int>(kv_stride) + 8 * n;
+  const int voff = 4 * q4 * static_cast<int>(kv_stride) + 8 * n;
 
   float m_run = -INFINITY, l_run = 0.f;
   f32x4 acc[kHeadDim / 16];
 #pragma unroll
   for (int t = 0; t < kHeadDim / 16; ++t) acc[t] = f32x4{};
 
-  const int slot0 = min(topk, (sp * kAttnWaves + wv) * slots_per_wave);
-  const int slot1 = min(topk, slot0 + slots_per_wave);
-  // the wave's block ids, one per lane, fetched at once (slots_per_wave <= 64 with ids)
-  const int my_b = ids && slot0 + lane < slot1 ? ids[slot0 + lane] : -1;
   // paged: each lane fetches the page of its slot's block up front (no table
   // read between a block's id and its loads)
   int32_t my_pg = 0;
   if constexpr (PAGED) {
     const int bb = ids ? my_b : slot0 + lane;
-    if (p >= 0 && slot0 + lane < slot1 && bb >= 0 && bb <= p / BK) my_pg = kbk.table[kbk.page_index(bb)];
+    if (p >= 0 && slot0 + lane < slot1 && bb >= 0 && bb <= p / kSub) my_pg = kbk.table[kbk.page_index(bb)];
   }
-  // 64-key blocks: each load instruction takes whole K rows (bf16: 4 rows of
-  // 256 bytes, 16 lanes per row; E4M3: 8 rows of 128 bytes) -- the rows are
-  // scattered at the cache's token stride, and whole rows per instruction are
-  // served faster than 64- or 32-byte pieces of 16 rows -- and the block goes
-  // through LDS into the MFMA operand layout (bf16: 111 -> 107 us per 128K
-  // decode step).  128-key blocks (equal or slower staged) load the operands
-  // directly.
-  constexpr bool kStageK = BK == 64;
-  Raw<T> ka[BK / 16][kHeadDim / 32];
-  u32x4 kw[sizeof(T) == 1 && kStageK ? BK / 8 : 1];     // E4M3 whole rows before staging
-  Raw<T> vraw[BK / 16][4];
+  // Each load instruction takes whole K rows (bf16: 4 rows of 256 bytes, 16
+  // lanes per row; E4M3: 8 rows of 128 bytes) -- the rows are scattered at the
+  // cache's token stride, and whole rows per instruction are served faster
+  // than 64- or 32-byte pieces of 16 rows -- and a slot goes through LDS into
+  // the MFMA operand layout (bf16: 111 -> 107 us per 128K decode step).
+  Raw<T> ka[kSub / 16][kHeadDim / 32];
+  u32x4 kw[sizeof(T) == 1 ? kSub / 8 : 1];     // E4M3 whole rows before staging
+  Raw<T> vraw[kSub / 16][4];
   // K and raw V of slot j (a valid slot of the current window) are requested;
   // the next valid slot's loads go out as soon as these registers are free
   // (K after the S^T MFMAs, V after its LDS staging), so they fly under this
   // block's softmax and O^T MFMAs.
   auto block_of = [&](int slot) { return ids ? __builtin_amdgcn_readlane(my_b, slot - slot0) : slot; };
+  // A slot's first key row relative to kbase / vbase and the sequence's rows
+  // from there on, in scalar registers: with all 64 rows there (all but a
+  // sequence's last slot) a load takes a scalar base and the lane's fixed
+  // offset.  Rows past the end re-read the last one (their weights are zero);
+  // that path's row numbers are formed from an opaque lane, or they are kept
+  // across the loop and spill (103 us against 99 at 64 x 128K).
   auto row_of = [&](int slot, int b) -> int64_t {
-    return PAGED ? kbk.block_row(__builtin_amdgcn_readlane(my_pg, slot - slot0), b) : 0;
+    if constexpr (PAGED) {
+      const int64_t row = kbk.block_row(__builtin_amdgcn_readlane(my_pg, slot - slot0), b);
+      return static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(row), 0));
+    } else {
+      return static_cast<int64_t>(b) * kSub;
+    }
   };
   auto load_k = [&](int slot) {
-    const int b = block_of(slot);
-    const int key0 = b * BK;
-    const int64_t page_row = row_of(slot, b);
-    if constexpr (kStageK && sizeof(T) == 1) {
+    const int b = __builtin_amdgcn_readfirstlane(block_of(slot));
+    const int rows = __builtin_amdgcn_readfirstlane(g.kv_len) - b * kSub;
+    const T* blk = kbase + row_of(slot, b) * kv_stride;
+    if constexpr (sizeof(T) == 1) {                         // lanes 8 (l / 8) .. + 7 take row 8 i + l / 8
+      if (rows >= kSub) {
 #pragma unroll
-      for (int i = 0; i < BK / 8; ++i) {
-        const int kr = 8 * i + (lane >> 3);                 // key row of this lane: lanes 8 (lane / 8) .. + 7
-        const int key = key0 + kr;
-        const T* kp = (PAGED ? krow_base + (page_row + kr) * kv_stride : krow_base + static_cast<int64_t>(key) * kv_stride) + 16 * (lane & 7);
-        kw[i] = key < g.kv_len ? *reinterpret_cast<const u32x4*>(kp) : u32x4{};
+        for (int i = 0; i < kSub / 8; ++i) kw[i] = *reinterpret_cast<const u32x4*>(blk + 8 * i * kv_stride + koff);
+      } else {
+#pragma unroll
+        for (int i = 0; i < kSub / 8; ++i)
+          kw[i] = *reinterpret_cast<const u32x4*>(blk + min(8 * i + (lane >> 3), rows - 1) * kv_stride + 16 * (lane & 7));
       }
-    } else if constexpr (kStageK) {
+    } else {                                                // lanes 16 q4 .. + 15 take row 16 i + 4 j + q4
+      if (rows >= kSub) {
 #pragma unroll
-      for (int i = 0; i < BK / 16; ++i)
+        for (int i = 0; i < kSub / 16; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int kr = 16 * i + 4 * j + q4;            // key row of this lane: lanes 16 q4 .. + 15
-          const int key = key0 + kr;
-          const T* kp = (PAGED ? krow_base + (page_row + kr) * kv_stride : krow_base + static_cast<int64_t>(key) * kv_stride) + 8 * n;
-          ka[i][j] = key < g.kv_len ? load_raw(kp) : Raw<T>{};
-        }
-    } else {
+          for (int j = 0; j < 4; ++j) ka[i][j] = load_raw(blk + (16 * i + 4 * j) * kv_stride + koff);
+      } else {
+        int l = lane;
+        asm volatile("" : "+v"(l));                         // not kept across the loop
 #pragma unroll
-      for (int i = 0; i < BK / 16; ++i) {
-        const int key = key0 + 16 * i + n;
-        const T* kp = PAGED ? kbase + (page_row + 16 * i + n) * kv_stride : kbase + static_cast<int64_t>(key) * kv_stride;
+        for (int i = 0; i < kSub / 16; ++i)
 #pragma unroll
-        for (int ks = 0; ks < kHeadDim / 32; ++ks) ka[i][ks] = key < g.kv_len ? load_raw(kp + 32 * ks) : Raw<T>{};
+          for (int j = 0; j < 4; ++j)
+            ka[i][j] = load_raw(blk + min(16 * i + 4 * j + (l >> 4), rows - 1) * kv_stride + 8 * (l & 15));
       }
     }
   };
-  auto load_v = [&](int slot) {
-    const int b = block_of(slot);
-    if constexpr (PAGED)
-      load_v_raw<BK, T>(vbase + row_of(slot, b) * kv_stride, kv_stride, 0, g.kv_len - b * BK, vraw);
-    else
-      load_v_raw<BK, T>(vbase, kv_stride, b * BK, g.kv_len, vraw);
+  auto load_v = [&](int slot) {                             // lane: rows 16 it + 4 q4 + j, dims 8 n ..
+    const int b = __builtin_amdgcn_readfirstlane(block_of(slot));
+    const int rows = __builtin_amdgcn_readfirstlane(g.kv_len) - b * kSub;
+    const T* blk = vbase + row_of(slot, b) * kv_stride;
+    if (rows >= kSub) {
+#pragma unroll
+      for (int it = 0; it < kSub / 16; ++it)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) vraw[it][j] = load_raw(blk + (16 * it + j) * kv_stride + voff);
+    } else {
+      int l = lane;
+      asm volatile("" : "+v"(l));
+#pragma unroll
+      for (int it = 0; it < kSub / 16; ++it)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          vraw[it][j] = load_raw(blk + min(16 * it + 4 * (l >> 4) + j, rows - 1) * kv_stride + 8 * (l & 15));
+    }
   };
   // windows of 64 slots (one slot per lane in the validity ballot)
   for (int w0 = slot0; w0 < slot1 && p >= 0; w0 += kWave) {
     const int bl = ids ? my_b : w0 + lane;
-    const bool vl = w0 + lane < slot1 && bl >= 0 && bl <= p / BK;
+    const bool vl = w0 + lane < slot1 && bl >= 0 && bl <= p / kSub;
     uint64_t pend = __ballot(vl);
     int slot = pend != 0ull ? w0 + __ffsll(static_cast<unsigned long long>(pend)) - 1 : -1;
     if (slot >= 0) {
@@ -220,36 +242,36 @@ __global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PA
       pend &= pend - 1;
       const int next = pend != 0ull ? w0 + __ffsll(static_cast<unsigned long long>(pend)) - 1 : -1;
       const int b = block_of(slot);
-      const int key0 = b * BK;
-      if constexpr (kStageK && sizeof(T) == 1) {
+      const int key0 = b * kSub;
+      if constexpr (sizeof(T) == 1) {
         wave_lds_order();                               // the previous block's V^T reads are done
   #pragma unroll
-        for (int i = 0; i < BK / 8; ++i) *reinterpret_cast<u32x4*>(&sm.kr8[8 * i + (lane >> 3)][16 * (lane & 7)]) = kw[i];
+        for (int i = 0; i < kSub / 8; ++i) *reinterpret_cast<u32x4*>(&sm.kr8[8 * i + (lane >> 3)][16 * (lane & 7)]) = kw[i];
         wave_lds_order();                               // K staged
   #pragma unroll
-        for (int i = 0; i < BK / 16; ++i)
+        for (int i = 0; i < kSub / 16; ++i)
   #pragma unroll
           for (int ks = 0; ks < kHeadDim / 32; ++ks)
             ka[i][ks] = *reinterpret_cast<const Raw<T>*>(&sm.kr8[16 * i + n][32 * ks + 8 * q4]);
       }
-      if constexpr (kStageK && sizeof(T) == 2) {
+      if constexpr (sizeof(T) == 2) {
         wave_lds_order();                               // the previous block's V^T reads are done
   #pragma unroll
-        for (int i = 0; i < BK / 16; ++i)
+        for (int i = 0; i < kSub / 16; ++i)
   #pragma unroll
           for (int j = 0; j < 4; ++j)
             *reinterpret_cast<Raw<T>*>(&sm.kr[16 * i + 4 * j + q4][8 * n]) = ka[i][j];
         wave_lds_order();                               // K staged
   #pragma unroll
-        for (int i = 0; i < BK / 16; ++i)
+        for (int i = 0; i < kSub / 16; ++i)
   #pragma unroll
           for (int ks = 0; ks < kHeadDim / 32; ++ks)
             ka[i][ks] = *reinterpret_cast<const Raw<T>*>(&sm.kr[16 * i + n][32 * ks + 8 * q4]);
       }
       // S^T tiles: keys 16i..16i+15 (rows) x heads (columns)
-      f32x4 st[BK / 16];
+      f32x4 st[kSub / 16];
   #pragma unroll
-      for (int i = 0; i < BK / 16; ++i) {
+      for (int i = 0; i < kSub / 16; ++i) {
         st[i] = f32x4{};
   #pragma unroll
         for (int ks = 0; ks < kHeadDim / 32; ++ks) st[i] = mfma16x16x32(widen_bf16x8(ka[i][ks]), bq[ks], st[i]);
@@ -258,7 +280,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PA
       // lane (n, q4) holds keys 16i + 4*q4 + e of head n
       float bmax = -INFINITY;
   #pragma unroll
-      for (int i = 0; i < BK / 16; ++i)
+      for (int i = 0; i < kSub / 16; ++i)
   #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int key = key0 + 16 * i + 4 * q4 + e;
@@ -273,7 +295,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PA
       const float alpha = exp2_hw(m_run - m_new);
       float lsum = 0.f;
   #pragma unroll
-      for (int i = 0; i < BK / 16; ++i)
+      for (int i = 0; i < kSub / 16; ++i)
   #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float pe = exp2_hw(st[i][e] - m_new);
@@ -288,14 +310,14 @@ __global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PA
       for (int t = 0; t < kHeadDim / 16; ++t) acc[t] *= alpha;
 
       wave_lds_order();                                 // the previous block's V^T reads are done
-      store_v_transposed<BK>(sm, vraw);
+      store_v_transposed(sm, vraw);
       if (next >= 0) load_v(next);
       // P^T as the B operand: k-step u covers keys 32u..32u+31; lane (n, q4)
       // supplies logical k = 8*q4 + e <-> key 32u + 4*q4 + e (e < 4) and
       // 32u + 16 + 4*q4 + e - 4 (e >= 4), exactly the keys its S^T tiles hold.
       wave_lds_order();                                 // V staged
   #pragma unroll
-      for (int u = 0; u < BK / 32; ++u) {
+      for (int u = 0; u < kSub / 32; ++u) {
         bf16x8 bp;
         {
           uint4 w;
@@ -389,7 +411,9 @@ __global__ __launch_bounds__(64 * kAttnWaves, (BK == 64 && sizeof(T) == 2 && !PA
 
 // Merge `nsplit` partials per (row, head): a = max LSE_s,
 // LSE = a + log sum exp(LSE_s - a), O = sum exp(LSE_s - LSE) O_s (Sec. 4.2).
-// One thread per (row, head, 8 dims).
+// One thread per (row, head, 8 dims); eight splits' LSEs and partials are
+// requested together (one after another, eight splits took 7.8 us for one row
+// of 64 heads) and folded into a running maximum.
 __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ o_part,
                                                       const float* __restrict__ lse_part, int nsplit,
                                                       int64_t head_rows, uint16_t* __restrict__ o,
@@ -398,31 +422,50 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
   const int64_t hr = tid >> 4;
   const int d0 = static_cast<int>(tid & 15) * 8;
   if (hr >= head_rows) return;
-  float a = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) a = fmaxf(a, lse_part[s * head_rows + hr]);
+  constexpr int kBatch = 8;
+  float a = -INFINITY, sum = 0.f;
   float out[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  float total = -INFINITY;
-  if (a > -INFINITY) {
-    float sum = 0.f;
-    for (int s = 0; s < nsplit; ++s) sum += exp2f((lse_part[s * head_rows + hr] - a) * kLog2e);
-    total = a + __logf(sum);
-    for (int s = 0; s < nsplit; ++s) {
-      const float ls = lse_part[s * head_rows + hr];
-      if (!(ls > -INFINITY)) continue;
-      const float w = exp2f((ls - total) * kLog2e);
-      const float4* src = reinterpret_cast<const float4*>(o_part + (s * head_rows + hr) * kHeadDim + d0);
-      const float4 x0 = src[0], x1 = src[1];
-      out[0] += w * x0.x; out[1] += w * x0.y; out[2] += w * x0.z; out[3] += w * x0.w;
-      out[4] += w * x1.x; out[5] += w * x1.y; out[6] += w * x1.z; out[7] += w * x1.w;
+  for (int s0 = 0; s0 < nsplit; s0 += kBatch) {
+    float l[kBatch];
+    f32x4 x[kBatch][2];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int64_t at = min(s0 + u, nsplit - 1) * head_rows + hr;
+      l[u] = lse_part[at];
+      const f32x4* src = reinterpret_cast<const f32x4*>(o_part + at * kHeadDim + d0);
+      x[u][0] = src[0];
+      x[u][1] = src[1];
+    }
+    float m = a;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      l[u] = s0 + u < nsplit ? l[u] : -INFINITY;
+      m = fmaxf(m, l[u]);
+    }
+    if (!(m > -INFINITY)) continue;                   // nothing visible so far
+    const float f = a > -INFINITY ? exp2f((a - m) * kLog2e) : 0.f;
+    a = m;
+    sum *= f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) out[e] *= f;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (!(l[u] > -INFINITY)) continue;              // an empty split's partial does not count
+      const float w = exp2f((l[u] - m) * kLog2e);
+      sum += w;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) out[e] += w * x[u][e >> 2][e & 3];
     }
   }
+  const bool any = a > -INFINITY;
+  const float inv = any ? 1.f / sum : 0.f;
   uint4 wv;
-  wv.x = pack_bf16x2(out[0], out[1]);
-  wv.y = pack_bf16x2(out[2], out[3]);
-  wv.z = pack_bf16x2(out[4], out[5]);
-  wv.w = pack_bf16x2(out[6], out[7]);
+  wv.x = pack_bf16x2(out[0] * inv, out[1] * inv);
+  wv.y = pack_bf16x2(out[2] * inv, out[3] * inv);
+  wv.z = pack_bf16x2(out[4] * inv, out[5] * inv);
+  wv.w = pack_bf16x2(out[6] * inv, out[7] * inv);
   *reinterpret_cast<uint4*>(o + hr * kHeadDim + d0) = wv;
-  if (d0 == 0) lse[hr] = total;
+  if (d0 == 0) lse[hr] = any ? a + __logf(sum) : -INFINITY;
 }
 
 // ---------------------------------------------------------------- host side
@@ -454,7 +497,7 @@ struct SplitPlan {
   int slots_per_wave;
 };
 
-// Spread the k slots of each (row, group) over kAttnWaves waves per CTA and
+// Spread the slots of each (row, group) over kAttnWaves waves per CTA and
 // over enough CTAs to give the chip about 2048 waves.
 SplitPlan split_plan(const msa_seqs* seqs, int H_kv, int topk) {
   SplitPlan sp;
@@ -475,10 +518,28 @@ size_t split_workspace(const msa_seqs* seqs, int H_q, const SplitPlan& sp) {
   return msa_host::align_up(sp.nsplit * hr * kHeadDim * sizeof(float), 256) + sp.nsplit * hr * sizeof(float);
 }
 
+int block_shift(int BK) { return BK == 128 ? 1 : 0; }    // log2 of slots per block
+
+// The decode call's split: over 64-key slots, or where the workspace is too
+// small for that many splits over whole blocks.
+int decode_plan(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk, const void* workspace,
+                size_t workspace_bytes, SplitPlan* sp) {
+  auto fits = [&]() {
+    const size_t need = split_workspace(seqs, H_q, *sp);
+    return need == 0 || (workspace && workspace_bytes >= need);
+  };
+  const int shift = block_shift(BK);
+  *sp = split_plan(seqs, H_kv, topk << shift);
+  if (fits()) return MSA_OK;
+  *sp = split_plan(seqs, H_kv, topk);
+  sp->slots_per_wave <<= shift;
+  return fits() ? MSA_OK : MSA_ERR_WORKSPACE;
+}
+
 // fp8: Q, K and V are OCP e4m3 with per-tensor scales (logits use
 // scale * q_scale * k_scale, O is multiplied by v_scale); else bf16 (scales 1).
 int run_rows(const void* q, const void* k, const void* v, const int32_t* block_ids, const msa_seqs* seqs,
-             int H_q, int H_kv, int BK, int topk, float scale, void* o, float* lse, const SplitPlan& sp,
+             int H_q, int H_kv, int sub_shift, int topk, float scale, void* o, float* lse, const SplitPlan& sp,
              void* workspace, hipStream_t stream, bool fp8 = false, float q_scale = 1.f, float k_scale = 1.f,
              float v_scale = 1.f) {
   const int64_t hr = seqs->total_q_rows * H_q;
@@ -498,18 +559,14 @@ int run_rows(const void* q, const void* k, const void* v, const int32_t* block_i
     using T = decltype(elem);
     msa_prof::launch("attn_rows_kernel", kernel, grid, block, 0, stream, static_cast<const T*>(q),
                      static_cast<const T*>(k), static_cast<const T*>(v), block_ids, sq, H_q, H_kv, topk,
-                     sp.slots_per_wave, sl2, v_scale, op, lse, o_part, lse_part);
+                     sub_shift, sp.slots_per_wave, sl2, v_scale, op, lse, o_part, lse_part);
   };
   if (sq.block_table) {
-    if (BK == 64 && !fp8) launch(attn_rows_kernel<64, uint16_t, true>, uint16_t{});
-    else if (BK == 64) launch(attn_rows_kernel<64, uint8_t, true>, uint8_t{});
-    else if (!fp8) launch(attn_rows_kernel<128, uint16_t, true>, uint16_t{});
-    else launch(attn_rows_kernel<128, uint8_t, true>, uint8_t{});
+    if (!fp8) launch(attn_rows_kernel<uint16_t, true>, uint16_t{});
+    else launch(attn_rows_kernel<uint8_t, true>, uint8_t{});
   } else {
-    if (BK == 64 && !fp8) launch(attn_rows_kernel<64, uint16_t, false>, uint16_t{});
-    else if (BK == 64) launch(attn_rows_kernel<64, uint8_t, false>, uint8_t{});
-    else if (!fp8) launch(attn_rows_kernel<128, uint16_t, false>, uint16_t{});
-    else launch(attn_rows_kernel<128, uint8_t, false>, uint8_t{});
+    if (!fp8) launch(attn_rows_kernel<uint16_t, false>, uint16_t{});
+    else launch(attn_rows_kernel<uint8_t, false>, uint8_t{});
   }
   if (sp.nsplit > 1) {
     const int64_t threads = hr * 16;
@@ -552,13 +609,13 @@ int msa_rows_dense(const void* q, const void* k, const void* v, const msa_seqs* 
   const size_t need = split_workspace(seqs, H_q, sp);
   if (need > 0 && (!workspace || workspace_bytes < need)) return MSA_ERR_WORKSPACE;
   const int nblk = (seqs->max_kv_len + 63) / 64 > 0 ? (seqs->max_kv_len + 63) / 64 : 1;
-  return run_rows(q, k, v, nullptr, seqs, H_q, H_kv, 64, nblk, scale, o, lse, sp, workspace, stream);
+  return run_rows(q, k, v, nullptr, seqs, H_q, H_kv, 0, nblk, scale, o, lse, sp, workspace, stream);
 }
 
 extern "C" size_t msa_sparse_attn_decode_workspace_size(const msa_seqs* seqs, int num_q_heads, int num_kv_heads,
                                                        int head_dim, int block_size, int topk) {
   if (validate_attn(seqs, num_q_heads, num_kv_heads, head_dim, block_size, topk) != MSA_OK) return 0;
-  return split_workspace(seqs, num_q_heads, split_plan(seqs, num_kv_heads, topk));
+  return split_workspace(seqs, num_q_heads, split_plan(seqs, num_kv_heads, topk << block_shift(block_size)));
 }
 
 extern "C" int msa_sparse_attn_decode(const void* q, const void* k, const void* v, const int32_t* block_ids,
@@ -569,10 +626,10 @@ extern "C" int msa_sparse_attn_decode(const void* q, const void* k, const void* 
   if (st != MSA_OK) return st;
   if (seqs->total_q_rows == 0) return MSA_OK;
   if ((st = check_ptrs(q, k, v, block_ids, o, lse)) != MSA_OK) return st;
-  const SplitPlan sp = split_plan(seqs, num_kv_heads, topk);
-  const size_t need = split_workspace(seqs, num_q_heads, sp);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return MSA_ERR_WORKSPACE;
-  return run_rows(q, k, v, block_ids, seqs, num_q_heads, num_kv_heads, block_size, topk, softmax_scale, o, lse,
+  SplitPlan sp;
+  if ((st = decode_plan(seqs, num_q_heads, num_kv_heads, block_size, topk, workspace, workspace_bytes, &sp)) != MSA_OK)
+    return st;
+  return run_rows(q, k, v, block_ids, seqs, num_q_heads, num_kv_heads, block_shift(block_size), topk, softmax_scale, o, lse,
                   sp, workspace, stream);
 }
 
@@ -622,10 +679,10 @@ extern "C" int msa_sparse_attn_decode_fp8(const void* q, const void* k, const vo
   if (!scale_ok(q_scale) || !scale_ok(k_scale) || !scale_ok(v_scale)) return MSA_ERR_INVALID;
   if (seqs->total_q_rows == 0) return MSA_OK;
   if ((st = check_ptrs(q, k, v, block_ids, o, lse)) != MSA_OK) return st;
-  const SplitPlan sp = split_plan(seqs, num_kv_heads, topk);
-  const size_t need = split_workspace(seqs, num_q_heads, sp);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return MSA_ERR_WORKSPACE;
-  return run_rows(q, k, v, block_ids, seqs, num_q_heads, num_kv_heads, block_size, topk, softmax_scale, o, lse,
+  SplitPlan sp;
+  if ((st = decode_plan(seqs, num_q_heads, num_kv_heads, block_size, topk, workspace, workspace_bytes, &sp)) != MSA_OK)
+    return st;
+  return run_rows(q, k, v, block_ids, seqs, num_q_heads, num_kv_heads, block_shift(block_size), topk, softmax_scale, o, lse,
                   sp, workspace, stream, true, q_scale, k_scale, v_scale);
 }
 
