@@ -437,8 +437,9 @@ __global__ __launch_bounds__(256) void index_block_max_wave_kernel(
 // operands through the wave's LDS rows) and more waves share each CU.
 // Lane (n, q4) supplies key 16i + n / row n and dims 32ks + 8q4 .. +8; C lane
 // (n, q4) holds row n, keys 16i + 4q4 + e.
-template <int D_IDX, int BK, int DEPTH, bool PAGED>
-__global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
+// A wave scores SB consecutive blocks.
+template <int D_IDX, int BK, int DEPTH, int SB, int WAVES, bool PAGED>
+__global__ __launch_bounds__(WAVES * kWave) void index_block_max_narrow_kernel(
     const uint16_t* __restrict__ index_q, const uint16_t* __restrict__ index_k, msa_seqs sq,
     int unit_shift, int H_kv, int qr, int64_t u0, int64_t u1, float* __restrict__ M,
     int64_t ldm) {
@@ -447,14 +448,14 @@ __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
   constexpr int MT = 4;                               // 16-key tiles per sub-block
   const int lane = lane_id();
   const int64_t uidx = u0 + blockIdx.y;
-  const int slice = blockIdx.x * kWaves + threadIdx.x / kWave;
+  const int slice = blockIdx.x * WAVES + threadIdx.x / kWave;
   if (uidx >= u1) return;
   UnitRows ur = locate_unit(sq, unit_shift, uidx, qr, 1);
   if (!ur.ok) return;
   const int p_last = ur.g.kv_len - ur.g.q_rows + ur.t0 + ur.nq - 1;
   if (p_last < 0) return;
   const int kb1 = min(p_last / BK, static_cast<int>(ldm));
-  const int kb0 = slice * kSliceBlocks;
+  const int kb0 = slice * SB;
   if (kb0 >= kb1) return;
 
   const int n = lane & 15, q4 = lane >> 4;
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
   // .. kb1-1 are entirely before every row's local block, hence inside the
   // sequence; loads past kb1 re-read block kb1-1.  Paged: lane i holds the
   // page of the slice's block i, fetched once.
-  const int64_t my_prow = PAGED ? kbk.template row_as<true>(min(kb0 + (lane % kSliceBlocks), kb1 - 1)) : 0;
+  const int64_t my_prow = PAGED ? kbk.template row_as<true>(min(kb0 + (lane % SB), kb1 - 1)) : 0;
   // A sub-block (64 contiguous keys of d_idx bf16) is loaded as whole rows,
   // lane l taking 16-byte unit 64 c + l of load c (1 KiB per load, instead
   // of 64-byte pieces of 16 rows: 192 -> 187 us per 128K decode step at
@@ -484,7 +485,7 @@ __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
   };
   // rows padded by 16 bytes: the operand reads (16 rows, one column) are
   // free of bank conflicts
-  __shared__ __align__(16) uint16_t ks_lds[kWaves][64][D_IDX + 8];
+  __shared__ __align__(16) uint16_t ks_lds[WAVES][64][D_IDX + 8];
   auto to_operands = [&](bf16x8 (&a)[MT][KS]) {
     auto& rows = ks_lds[threadIdx.x / kWave];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the previous sub-block's reads are done
@@ -504,9 +505,9 @@ __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
   bf16x8 buf[DEPTH][MT][KS];
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) load_a(d, buf[d]);
-  float mb[kSliceBlocks];
+  float mb[SB];
 #pragma unroll
-  for (int j = 0; j < kSliceBlocks * HB; ++j) {
+  for (int j = 0; j < SB * HB; ++j) {
     bf16x8 (&a)[MT][KS] = buf[j % DEPTH];
     to_operands(a);
     f32x4 acc[MT];
@@ -524,14 +525,14 @@ __global__ __launch_bounds__(256) void index_block_max_narrow_kernel(
     m = fmaxf(m, __uint_as_float(xor_lane_u32<16>(__float_as_uint(m))));
     m = fmaxf(m, __uint_as_float(xor_lane_u32<32>(__float_as_uint(m))));
     mb[j / HB] = j % HB == 0 ? m : fmaxf(mb[j / HB], m);
-    if (j + DEPTH < kSliceBlocks * HB) load_a(j + DEPTH, a);
+    if (j + DEPTH < SB * HB) load_a(j + DEPTH, a);
   }
   // values past kb1 are never read (they are >= every row's local block) and
   // stay inside this slice; quads start below ldm (a multiple of 4)
   if (lane < nvalid) {
     float* mrow = M + ((uidx - u0) * kWave + lane) * ldm + kb0;
 #pragma unroll
-    for (int q = 0; q < kSliceBlocks / 4; ++q)
+    for (int q = 0; q < SB / 4; ++q)
       if (kb0 + 4 * q < ldm)
         *reinterpret_cast<float4*>(mrow + 4 * q) = make_float4(mb[4 * q], mb[4 * q + 1], mb[4 * q + 2], mb[4 * q + 3]);
   }
@@ -639,18 +640,8 @@ __device__ __forceinline__ void stream_chunks(Load load, int nscan, int c_begin,
   }
 }
 
-// The row's best keys of chunks c_begin, c_begin + c_step, ..., sorted
-// descending across the lanes (at least the best K1 are exact); keys are
-// inserted one chunk at a time.
-template <typename Load>
-__device__ __forceinline__ uint64_t scan_row_chunks(Load load, int nscan, int K1, int c_begin, int c_step) {
-  uint64_t list = 0;
-  if (K1 <= 0) return list;
-  stream_chunks(load, nscan, c_begin, c_step, [&](uint64_t v, uint64_t t) { return insert_keys(v, t, K1, list); });
-  return list;
-}
-
-// The same selection through a KeyBatch.
+// The row's best keys (at least the best K1), sorted descending across the
+// lanes, through a KeyBatch.
 template <typename Load>
 __device__ __forceinline__ uint64_t scan_row_batched(Load load, int nscan, KeyBatch& kb) {
   kb.list = 0;
@@ -1097,15 +1088,16 @@ __global__ __launch_bounds__(256) void index_topk_kernel(
   finish_row(list, topk - 1, t.lb, topk, t.out);
 }
 
-// kSplitWaves waves per index row (for few rows): wave w scans chunks w,
-// w + kSplitWaves, ...; the partial lists are merged pairwise through LDS in
-// log2(kSplitWaves) steps.
+// kSplitWaves waves per index row (few long rows with a large k): each takes the
+// best of a consecutive share of the row; the sorted lists are merged pairwise
+// through LDS in log2(kSplitWaves) steps.
 constexpr int kSplitWaves = 16;
 
 __global__ __launch_bounds__(64 * kSplitWaves) void index_topk_split_kernel(
     const float* __restrict__ M, int64_t ldm, msa_seqs sq, int unit_shift, int H_kv,
     int qr, int U, int rpu, int64_t u0, int64_t u1, int BK, int topk, int32_t* __restrict__ block_ids) {
   __shared__ uint64_t lists[kSplitWaves][kWave];
+  __shared__ uint64_t s_buf[kSplitWaves][2 * kWave];
   const int lane = lane_id();
   const int w = threadIdx.x / kWave;
   const int64_t task = blockIdx.x;
@@ -1118,7 +1110,15 @@ __global__ __launch_bounds__(64 * kSplitWaves) void index_topk_split_kernel(
   }
   const int K1 = topk - 1;
   const float* mrow = t.mrow;
-  uint64_t list = scan_row_chunks([=](int b) { return mrow[b]; }, t.nscan, K1, w, kSplitWaves);
+  const int seg = (t.nscan + 4 * kSplitWaves - 1) / (4 * kSplitWaves) * 4;     // float4 loads: whole quads
+  const int b0 = w * seg;
+  uint64_t list = 0ull;
+  if (K1 > 0 && b0 < t.nscan) {
+    list = row_best_keys<true, 8>(mrow + b0, min(seg, t.nscan - b0), K1, s_buf[w]);
+    if (lane < K1 && list != 0ull) list -= b0;       // columns of the row: a key's low word falls as the column rises
+    else list = 0ull;
+  }
+  list = wave_sort_desc_u64(list);
   lists[w][lane] = list;
   // step s: wave w (a multiple of 2s) merges in wave w + s's list, written at
   // the previous step; the barrier orders the steps
@@ -1252,6 +1252,27 @@ __global__ __launch_bounds__(kRowWaves * kWave) void index_topk_rows_kernel(
   finish_row(list, K1, t.lb, topk, t.out);
 }
 
+// One wave per CTA and index row, RP values per lane and round: fewer rows than
+// the chip has SIMDs each get one to themselves.
+template <int RP>
+__global__ __launch_bounds__(kWave) void index_topk_one_wave_kernel(
+    const float* __restrict__ M, int64_t ldm, msa_seqs sq, int unit_shift, int H_kv, int qr,
+    int U, int rpu, int64_t u0, int64_t u1, int BK, int topk, int32_t* __restrict__ block_ids) {
+  __shared__ uint64_t s_buf[2 * kWave];
+  const int lane = lane_id();
+  const int64_t task = blockIdx.x;
+  if (task >= (u1 - u0) * rpu) return;
+  const RowTask t = locate_row(M, ldm, sq, unit_shift, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
+  if (!t.ok) return;
+  if (t.no_position) {
+    if (lane < topk) t.out[lane] = -1;
+    return;
+  }
+  const int K1 = topk - 1;
+  const uint64_t list = K1 > 0 ? row_best_keys<true, RP>(t.mrow, t.nscan, K1, s_buf) : 0ull;
+  finish_row(list, K1, t.lb, topk, t.out);
+}
+
 // The min(n, K) best of n scores, n <= 2 kWave, from registers.
 __device__ __forceinline__ uint64_t short_row_best_keys(const float* __restrict__ srow, int n, int K, uint64_t* buf) {
   const int lane = lane_id();
@@ -1326,18 +1347,37 @@ int make_plan(const msa_seqs* seqs, int H_kv, int d_idx, int BK, int topk, Index
 constexpr int64_t kMinScoreCtas = 1024;                  // fewer slices: CTAs take pieces of them
 constexpr size_t kDefaultScoreBytes = size_t(4) << 30;   // block-score staging per call
 constexpr int64_t kSplitTopkRows = 4096;                 // fewer index rows: no chunk / piece maxima
-// Few rows go one wave per row (index_topk_rows_kernel) when the rows are
-// short (at most 4 rounds of 2048 blocks), numerous enough to spread and the
-// Top-k small enough for the lane-maximum bound to keep a round's candidates
-// within the wave's buffer; otherwise 16 waves share each row
-// (index_topk_split_kernel).
+// Few rows go one wave per row, four to a CTA, where the rows are short (at most 4
+// rounds of 2048 blocks), numerous enough to spread and the Top-k small enough for
+// the lane-maximum bound to keep a round's candidates within the wave's buffer
+// (index_topk_rows_kernel); fewer rows or a larger k, one wave in a CTA of its own
+// up to one round, 16 waves per row beyond (index_topk_split_kernel).  Scores and
+// Top-k of one row of 8 groups of 64-key blocks, one wave against 16: 7.7 and 11 us
+// at 8K, 12 and 15 at 130K (2032 blocks), k 16; 30 and 24 at 520K, k 24 and 48.
 constexpr int kRowTopkMaxK = 33;
 constexpr int64_t kRowTopkMinRows = 64;
 constexpr int kRowTopkMaxBlocks = 4 * 2048;
+constexpr int kOneWaveMaxBlocks = 2048;
 
 // 64-key sub-blocks in flight per wave of the narrow kernel: about 128 VGPRs of K_idx.
 template <int D, int B>
 constexpr int kNarrowDepth = D == 64 ? 4 : 2;
+
+// Narrow kernel: up to three rounds of slices (of the 2048 waves the chip holds
+// with d_idx 128), waves take pieces of 4 blocks in CTAs of their own: the few
+// waves' chains of rounds are the time of small calls, and CTAs of one wave
+// spread evenly over the CUs and leave no long last round.  With their Top-k,
+// slices in CTAs of four against pieces in CTAs of one: d_idx 128, 128-key
+// blocks, one row at 8K 20.4 and 10.4 us, 36 rows at 65K 144 and 114, 64 rows of
+// 48K to 131K 244 and 242; d_idx 64, 64-key blocks, one row at 8K 10.3 and 7.7.
+// Longer calls stream the same with less setup in slices (64 rows at 131K, d_idx
+// 64: 196 and 208 us).  (The worst place found for pieces: 17 rows at 32K, d_idx
+// 128, read from the last-level cache, 28.7 and 32.7.)
+constexpr int64_t kNarrowPieceMaxSlices = 3 * 2048;
+constexpr int kNarrowPieceBlocks = 4;
+bool narrow_pieces(const IndexPlan& pl, int64_t units) {
+  return pl.narrow && units * ((pl.bcap + kSliceBlocks - 1) / kSliceBlocks) < kNarrowPieceMaxSlices;
+}
 
 template <int D, int B, bool PAGED>
 void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const uint16_t* iq, const uint16_t* ik,
@@ -1355,9 +1395,15 @@ void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const 
     msa_prof::launch("index_block_max_lds_kernel", (index_block_max_lds_kernel<D, B, 64, PAGED>), grid, dim3(256), 0,
                      stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, cta_blocks, M, static_cast<int64_t>(pl.bcap), CM,
                      cm_stride, PM);
+  else if (narrow_pieces(pl, u1 - u0))
+    msa_prof::launch("index_block_max_narrow_kernel",
+                     (index_block_max_narrow_kernel<D, B, kNarrowDepth<D, B>, kNarrowPieceBlocks, 1, PAGED>), grid,
+                     dim3(kWave), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
+                     static_cast<int64_t>(pl.bcap));
   else if (pl.narrow)
-    msa_prof::launch("index_block_max_narrow_kernel", (index_block_max_narrow_kernel<D, B, kNarrowDepth<D, B>, PAGED>),
-                     grid, dim3(256), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
+    msa_prof::launch("index_block_max_narrow_kernel",
+                     (index_block_max_narrow_kernel<D, B, kNarrowDepth<D, B>, kSliceBlocks, kWaves, PAGED>), grid,
+                     dim3(kWaves * kWave), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
                      static_cast<int64_t>(pl.bcap));
   else
     msa_prof::launch("index_block_max_wave_kernel", (index_block_max_wave_kernel<D, B, PAGED>), grid, dim3(256), 0,
@@ -1408,8 +1454,6 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
   const uint16_t* iq = static_cast<const uint16_t*>(index_q);
   const uint16_t* ik = static_cast<const uint16_t*>(index_k);
 
-  // per-wave kernel: slices of kSliceBlocks consecutive blocks, 4 per CTA
-  const int nslice = (pl.bcap + kSliceBlocks - 1) / kSliceBlocks;
   for (int64_t u0 = 0; u0 < pl.max_units; u0 += chunk) {
     const int64_t u1 = u0 + chunk < pl.max_units ? u0 + chunk : pl.max_units;
     // a CTA scores a 64-block slice, or a 16-block piece where slices would
@@ -1418,8 +1462,13 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
     const int cta_blocks = (u1 - u0) * slices < kMinScoreCtas ? kPieceBlocks : kBlocksPerCta;
     const unsigned ny = static_cast<unsigned>((pl.bcap + cta_blocks - 1) / cta_blocks);
     float* cm = cta_blocks == kBlocksPerCta ? CM : nullptr;
+    // per-wave kernels: slices (or pieces) of consecutive blocks, one per wave
+    const bool pieces = narrow_pieces(pl, u1 - u0);
+    const int wave_blocks = pieces ? kNarrowPieceBlocks : kSliceBlocks;
+    const int cta_waves = pieces ? 1 : kWaves;
+    const int nslice = (pl.bcap + wave_blocks - 1) / wave_blocks;
     const dim3 grid = pl.U >= kWaves ? dim3(static_cast<unsigned>(u1 - u0), ny)
-                                     : dim3(static_cast<unsigned>((nslice + kWaves - 1) / kWaves),
+                                     : dim3(static_cast<unsigned>((nslice + cta_waves - 1) / cta_waves),
                                             static_cast<unsigned>(u1 - u0));
     if (d_idx == 64 && block_size == 64)
       launch_scores<64, 64>(pl, grid, stream, iq, ik, sq, unit_shift, num_kv_heads, u0, u1, cta_blocks, M, cm, cm_stride, PM);
@@ -1439,6 +1488,13 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
                        dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), dim3(kRowWaves * kWave), 0,
                        stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0, u1,
                        block_size, topk, block_ids);
+    else if (rows <= kSplitTopkRows && pl.bcap <= kOneWaveMaxBlocks)
+      msa_prof::launch("index_topk_split_kernel",
+                       pl.bcap <= 8 * kWave    ? index_topk_one_wave_kernel<8>
+                       : pl.bcap <= 16 * kWave ? index_topk_one_wave_kernel<16>
+                                               : index_topk_one_wave_kernel<32>,
+                       dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, M, static_cast<int64_t>(pl.bcap), sq,
+                       unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0, u1, block_size, topk, block_ids);
     else if (rows <= kSplitTopkRows)
       msa_prof::launch("index_topk_split_kernel", index_topk_split_kernel, dim3(static_cast<unsigned>(rows)),
                        dim3(64 * kSplitWaves), 0, stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift,

@@ -126,6 +126,14 @@ INDEX_CASES = [
     ("rows_of_511_to_513_blocks", [140], [513 * 64 + 40], 2, 64, 64, False),
     ("rows_of_1023_to_1025_blocks", [140], [1025 * 64 + 40], 2, 64, 33, False),
     ("units_of_many_sequences", [33, 0, 70, 1, 129, 64, 65] * 10, [300, 5, 900, 64, 129, 64, 2000] * 10, 8, 64, 5, False),
+    # decode: waves of 4 blocks, one wave per row up to 2048 blocks, 16 beyond
+    ("decode_piece_edges", [1, 2, 1, 1, 1], [1, 256 + 64, 5 * 64, 64 * 64 + 1, 512 * 64 + 7], 8, 64, 16, False),
+    ("decode_one_wave_ties", [1, 1, 1], [513 * 64 + 9, 1025 * 64 + 9, 130], 4, 64, 64, True),
+    ("decode_one_wave_k64", [1, 1], [2049 * 64, 1030 * 64], 8, 64, 64, False),
+    ("decode_16_waves", [1, 1], [2050 * 64, 2100 * 64 + 3], 4, 64, 17, False),
+    ("decode_16_waves_ties", [1], [2200 * 64 + 3], 2, 64, 48, True),
+    ("decode_wide_pieces", [1, 3, 1], [77 * 128 + 1, 128 * 9, 300], 4, 128, 12, False),
+    ("decode_many_units_slices", [1] * 200, [256 * 64 + 5] + [700] * 199, 8, 64, 8, False),
 ]
 
 
