@@ -111,7 +111,8 @@ def _check(status: int, what: str):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle itself: building a torch.cuda.Stream object took 2.8 us of a call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -119,6 +120,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _need(t: torch.Tensor, name: str, dtype: torch.dtype, shape: Sequence[int], device):
+    if t.dtype == dtype and t.shape == shape and t.is_contiguous() and t.device == device:
+        return
     if t.dtype != dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if tuple(t.shape) != tuple(shape):
@@ -191,7 +194,8 @@ def index_topk(index_q: torch.Tensor, index_k: torch.Tensor, seqs: Seqs, block_s
     _need(index_k, "index_k", torch.bfloat16, (seqs.total_kv_rows, d_idx), dev)
     if out is None:
         out = torch.empty((Tq, H_kv, topk), dtype=torch.int32, device=dev)
-    _need(out, "block_ids", torch.int32, (Tq, H_kv, topk), dev)
+    else:
+        _need(out, "block_ids", torch.int32, (Tq, H_kv, topk), dev)
     nbytes = index_topk_workspace_size(seqs, H_kv, d_idx, block_size, topk)
     ws = _workspace(nbytes, dev, workspace)
     st = lib().msa_index_topk(_ptr(index_q), _ptr(index_k), seqs.ref(), H_kv, d_idx, block_size, topk,
@@ -233,7 +237,8 @@ def block_topk(scores: torch.Tensor, k: int, out: Optional[torch.Tensor] = None)
     dev = scores.device
     if out is None:
         out = torch.empty((n_rows, k), dtype=torch.int32, device=dev)
-    _need(out, "ids", torch.int32, (n_rows, k), dev)
+    else:
+        _need(out, "ids", torch.int32, (n_rows, k), dev)
     st = lib().msa_block_topk(_ptr(scores), n_rows, n_cols, ld, k, _ptr(out), _stream())
     _check(st, "msa_block_topk")
     return out
@@ -251,10 +256,12 @@ def _attn(kind: str, q, k, v, block_ids, seqs: Seqs, block_size: int, softmax_sc
     _need(block_ids, "block_ids", torch.int32, (Tq, H_kv, topk), dev)
     if out is None:
         out = torch.empty((Tq, H_q, d_h), dtype=torch.bfloat16, device=dev)
+    else:
+        _need(out, "o", torch.bfloat16, (Tq, H_q, d_h), dev)
     if lse is None:
         lse = torch.empty((Tq, H_q), dtype=torch.float32, device=dev)
-    _need(out, "o", torch.bfloat16, (Tq, H_q, d_h), dev)
-    _need(lse, "lse", torch.float32, (Tq, H_q), dev)
+    else:
+        _need(lse, "lse", torch.float32, (Tq, H_q), dev)
     scale = 1.0 / math.sqrt(d_h) if softmax_scale is None else float(softmax_scale)
     L = lib()
     nbytes = int(getattr(L, f"msa_sparse_attn_{kind}_workspace_size")(seqs.ref(), H_q, H_kv, d_h, block_size, topk))
@@ -300,10 +307,12 @@ def _attn_fp8(kind: str, q, k, v, scales, block_ids, seqs: Seqs, block_size: int
     _need(block_ids, "block_ids", torch.int32, (Tq, H_kv, topk), dev)
     if out is None:
         out = torch.empty((Tq, H_q, d_h), dtype=torch.bfloat16, device=dev)
+    else:
+        _need(out, "o", torch.bfloat16, (Tq, H_q, d_h), dev)
     if lse is None:
         lse = torch.empty((Tq, H_q), dtype=torch.float32, device=dev)
-    _need(out, "o", torch.bfloat16, (Tq, H_q, d_h), dev)
-    _need(lse, "lse", torch.float32, (Tq, H_q), dev)
+    else:
+        _need(lse, "lse", torch.float32, (Tq, H_q), dev)
     scale = 1.0 / math.sqrt(d_h) if softmax_scale is None else float(softmax_scale)
     L = lib()
     nbytes = int(getattr(L, f"msa_sparse_attn_{kind}_workspace_size")(seqs.ref(), H_q, H_kv, d_h, block_size, topk))
@@ -342,10 +351,12 @@ def dense_attn(q, k, v, seqs: Seqs, softmax_scale=None, out=None, lse=None, work
     _need(v, "v", torch.bfloat16, (seqs.total_kv_rows, H_kv, d_h), dev)
     if out is None:
         out = torch.empty((Tq, H_q, d_h), dtype=torch.bfloat16, device=dev)
+    else:
+        _need(out, "o", torch.bfloat16, (Tq, H_q, d_h), dev)
     if lse is None:
         lse = torch.empty((Tq, H_q), dtype=torch.float32, device=dev)
-    _need(out, "o", torch.bfloat16, (Tq, H_q, d_h), dev)
-    _need(lse, "lse", torch.float32, (Tq, H_q), dev)
+    else:
+        _need(lse, "lse", torch.float32, (Tq, H_q), dev)
     scale = 1.0 / math.sqrt(d_h) if softmax_scale is None else float(softmax_scale)
     nbytes = dense_attn_workspace_size(seqs, H_q, H_kv, d_h)
     ws = _workspace(nbytes, dev, workspace)
