@@ -36,7 +36,6 @@ using namespace msa;
 
 constexpr int kWaves = 4;
 constexpr int kBlocksPerCta = 64;      // key blocks per CTA slice, LDS kernel
-constexpr int kSmallInsert = 6;        // survivors per 64-block step inserted one by one
 
 // ---------------------------------------------------------------- units
 // A unit holds 2^unit_shift query rows of one sequence; sequence s owns units
@@ -539,32 +538,9 @@ __global__ __launch_bounds__(WAVES * kWave) void index_block_max_narrow_kernel(
 }
 
 // ---------------------------------------------------------------- top-k
-// Inserts the keys v (one per lane; 0 = none) that beat `thr` into `list`
-// (sorted descending across lanes) and returns the new K1-th best key.
-__device__ __forceinline__ uint64_t insert_keys(uint64_t v, uint64_t thr, int K1, uint64_t& list) {
-  const int lane = lane_id();
-  uint64_t pass = __ballot(v > thr);
-  if (pass == 0) return readlane_u64(list, K1 - 1);
-  if (__popcll(pass) <= kSmallInsert) {
-    while (pass) {
-      const int src = __ffsll(static_cast<unsigned long long>(pass)) - 1;
-      pass &= pass - 1;
-      const uint64_t xk = readlane_u64(v, src);
-      const int rnk = __popcll(__ballot(list > xk));
-      const uint64_t prev = lane_shr1_u64(list, list);
-      list = lane < rnk ? list : (lane == rnk ? xk : prev);
-    }
-  } else {
-    const uint64_t vs = wave_sort_desc_u64(v > thr ? v : 0ull);
-    const uint64_t rev = shfl_u64(vs, kWave - 1 - lane);
-    list = wave_bitonic_merge_desc_u64(list > rev ? list : rev);
-  }
-  return readlane_u64(list, K1 - 1);
-}
-
 // Keys that beat the running threshold are appended to a per-wave LDS
 // buffer (128 entries) and merged into the sorted list 64 at a time: one
-// bitonic sort + merge per 64 candidates instead of one insertion each.  The
+// bitonic sort + merge per 64 candidates.  The
 // threshold only rises at a merge, so some extra keys are buffered; the list
 // after flush() is still exactly the best K1 (and more) of all pushed keys.
 struct KeyBatch {
@@ -611,11 +587,10 @@ struct KeyBatch {
   }
 };
 
-// Streams chunks c_begin, c_begin + c_step, ... (64 scores each) of one row,
-// score b read as load(b), and hands each chunk's keys to ins(v, tau) (which
-// returns the new threshold).
+// Streams the chunks (64 scores each) of one row, score b read as load(b), and
+// hands each chunk's keys to ins(v, tau) (which returns the new threshold).
 template <typename Load, typename Ins>
-__device__ __forceinline__ void stream_chunks(Load load, int nscan, int c_begin, int c_step, Ins ins) {
+__device__ __forceinline__ void stream_chunks(Load load, int nscan, Ins ins) {
   const int lane = lane_id();
   uint64_t tau = 0;    // key of the K1-th best so far (0 while fewer are known)
   // block scores of the next kAhead chunks are in flight while one is ranked
@@ -623,16 +598,16 @@ __device__ __forceinline__ void stream_chunks(Load load, int nscan, int c_begin,
   float pf[kAhead];
 #pragma unroll
   for (int a = 0; a < kAhead; ++a) {
-    const int b = (c_begin + a * c_step) * kWave + lane;
+    const int b = a * kWave + lane;
     pf[a] = b < nscan ? load(b) : 0.f;
   }
-  for (int c = c_begin; c * kWave < nscan; c += c_step) {
+  for (int c = 0; c * kWave < nscan; ++c) {
     const int b = c * kWave + lane;
     const float x = pf[0];
 #pragma unroll
     for (int a = 0; a + 1 < kAhead; ++a) pf[a] = pf[a + 1];
     {
-      const int bn = (c + kAhead * c_step) * kWave + lane;
+      const int bn = (c + kAhead) * kWave + lane;
       pf[kAhead - 1] = bn < nscan ? load(bn) : 0.f;
     }
     const uint64_t v = b < nscan ? rank_key(x, static_cast<uint32_t>(b)) : 0ull;
@@ -647,7 +622,7 @@ __device__ __forceinline__ uint64_t scan_row_batched(Load load, int nscan, KeyBa
   kb.list = 0;
   kb.cnt = 0;
   if (kb.K1 <= 0) return 0;
-  stream_chunks(load, nscan, 0, 1, [&](uint64_t v, uint64_t t) { return kb.push(v, t); });
+  stream_chunks(load, nscan, [&](uint64_t v, uint64_t t) { return kb.push(v, t); });
   kb.flush();
   return kb.list;
 }
@@ -1222,7 +1197,7 @@ __device__ __forceinline__ uint64_t row_best_keys(const float* __restrict__ srow
   kb.K1 = k;
   kb.list = 0;
   kb.cnt = 0;
-  stream_chunks([=](int b) { return srow[b]; }, n, 0, 1, [&](uint64_t v, uint64_t th) { return kb.push(v, th); });
+  stream_chunks([=](int b) { return srow[b]; }, n, [&](uint64_t v, uint64_t th) { return kb.push(v, th); });
   kb.flush();
   return kb.list;
 }

@@ -166,15 +166,6 @@ __device__ __forceinline__ void store_transposed_pairs(uint16_t (*dst)[P], int d
   *reinterpret_cast<uint32_t*>(&dst[dd + 3][c0]) = (ev1 >> 16) | (od1 & 0xFFFF0000u);
 }
 
-// Value of lane - 1 (lane 0 receives `fill`): DPP wave shift right by one.
-__device__ __forceinline__ uint64_t lane_shr1_u64(uint64_t v, uint64_t fill) {
-  const int lo = __builtin_amdgcn_update_dpp(static_cast<int>(static_cast<uint32_t>(fill)),
-                                             static_cast<int>(static_cast<uint32_t>(v)), 0x138, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(static_cast<int>(static_cast<uint32_t>(fill >> 32)),
-                                             static_cast<int>(static_cast<uint32_t>(v >> 32)), 0x138, 0xF, 0xF, false);
-  return (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo);
-}
-
 // One compare-exchange step of a bitonic network: lanes with (lane & J) == 0
 // keep the max when `desc` else the min; their partners the other one.
 template <int J>
