@@ -188,7 +188,8 @@ int msa_block_topk(const float* scores, int64_t n_rows, int n_cols, int64_t ld, 
  *
  * Sec. 3.1, sparse-attention equation: for query row i and query head h of
  * group r = h / (num_q_heads / num_kv_heads), softmax attention with scale
- * `softmax_scale` (the paper uses 1/sqrt(head_dim)) over the causally visible
+ * `softmax_scale` (the paper uses 1/sqrt(head_dim); any finite value, zero and
+ * negative ones included, in every call that takes one) over the causally visible
  * tokens (j <= i) of the blocks listed in block_ids[i, r, :], using key/value
  * head r.  Entries < 0 are padding; the ids of a row must be distinct; ids
  * past the local block select no token.  Every row must list a block with a

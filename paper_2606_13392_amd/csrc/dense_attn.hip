@@ -54,7 +54,7 @@ extern "C" int msa_dense_attn(const void* q, const void* k, const void* v, const
   if (st != MSA_OK) return st;
   if (seqs->total_q_rows == 0) return MSA_OK;
   if (!q || !k || !v || !o || !lse) return MSA_ERR_INVALID;
-  const float scale = softmax_scale * kLog2e;
+  const flash::LogitScale scale = flash::logit_scale(softmax_scale * kLog2e);
   if (decode_like(seqs))
     return msa_rows_dense(q, k, v, seqs, num_q_heads, num_kv_heads, softmax_scale, o, lse, workspace,
                           workspace_bytes, stream);
@@ -69,6 +69,6 @@ extern "C" int msa_dense_attn(const void* q, const void* k, const void* v, const
   msa_prof::launch("dense_prefill_kernel", kernel, dim3(static_cast<unsigned>(tiles * num_kv_heads)),
                    dim3(kWaves * kWave), 0, stream, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                    static_cast<const uint16_t*>(v), static_cast<const int32_t*>(nullptr), *seqs, gr, num_q_heads,
-                   num_kv_heads, 0, 0, scale, 1.f, static_cast<uint16_t*>(o), lse);
+                   num_kv_heads, 0, 0, scale.log2, scale.q_flip, 1.f, static_cast<uint16_t*>(o), lse);
   return msa_host::launch_status();
 }

@@ -27,6 +27,8 @@
 #pragma once
 
 #include <algorithm>
+#include <cfloat>
+#include <cmath>
 #include <type_traits>
 
 #include "msa_common.h"
@@ -134,6 +136,19 @@ __device__ __forceinline__ void locate_tile(const msa_seqs& sq, const Grid& gr, 
   *tile = x - (sq.q_offsets[lo] / qt + lo);
 }
 
+// The kernel masks and takes maxima of raw scores, so its scale is positive: a
+// negative one flips the signs of Q (S and the scale change sign together,
+// exactly), and a zero one becomes the smallest normal number (no exponent of
+// scores below 2^100 then differs from 0 by more than 2^-26).
+struct LogitScale {
+  float log2;                            // > 0 (NaN stays)
+  uint32_t q_flip;                       // XORed into bf16 pairs of Q
+};
+inline LogitScale logit_scale(float scale_log2) {
+  const float a = std::fabs(scale_log2);
+  return LogitScale{a < FLT_MIN ? FLT_MIN : a, scale_log2 < 0.f ? 0x80008000u : 0u};
+}
+
 // T: element type of q, k and v (uint16_t = bf16 bits, uint8_t = e4m3 bits;
 // o_scale multiplies O).  SPARSE: block ids of BK keys per (row, group), rows
 // at positions below p_cut (at most kMaxBlocks * BK); else every causal key.
@@ -145,7 +160,7 @@ template <typename T, int BK, bool SPARSE, bool PAGED, int WAVES>
 __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ block_ids, msa_seqs sq, Grid gr, int H_q, int H_kv, int topk, int p_cut,
-    float scale_log2, float o_scale, uint16_t* __restrict__ o, float* __restrict__ lse) {
+    float scale_log2, uint32_t q_flip, float o_scale, uint16_t* __restrict__ o, float* __restrict__ lse) {
   constexpr int SUB = BK / kSub;           // 64-key sub-blocks per block
   constexpr int kThreads = WAVES * kWave;
   constexpr int MT = kSub / 32;            // 32-key tiles of S^T
@@ -546,7 +561,7 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
       if (nvisit > 1) store(r2, false, ring.k[1]);
     }
 #pragma unroll
-    for (int st = 0; st < KS; ++st) bq[st] = widen_bf16x8(rq[st]);
+    for (int st = 0; st < KS; ++st) bq[st] = __builtin_bit_cast(bf16x8, widen(rq[st]) ^ q_flip);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     {

@@ -63,10 +63,11 @@ int launch_tiles(const void* q, const void* k, const void* v, const int32_t* blo
   const int qt = kTileWaves * (32 / (H_q / H_kv));
   int64_t tiles;
   const flash::Grid gr = flash::plan_grid(seqs, qt, p_cut, &tiles);
+  const flash::LogitScale scale = flash::logit_scale(scale_log2);
   const auto kernel = flash::flash_tile_kernel<T, BK, true, PAGED, kTileWaves>;
   msa_prof::launch("tile_attn_kernel", kernel, dim3(static_cast<unsigned>(tiles * H_kv)), dim3(kTileWaves * kWave), 0,
                    stream, static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v), block_ids,
-                   *seqs, gr, H_q, H_kv, topk, p_cut, scale_log2, o_scale, static_cast<uint16_t*>(o), lse);
+                   *seqs, gr, H_q, H_kv, topk, p_cut, scale.log2, scale.q_flip, o_scale, static_cast<uint16_t*>(o), lse);
   return MSA_OK;
 }
 
