@@ -39,6 +39,9 @@
 //     bwd_dq_combine per (row, group): the valid slots' partials in slot order,
 //                    times scale, to bf16 dQ
 //   bwd_kv_convert   accumulators (dK times scale) to bf16 dK, dV
+#include <cfloat>
+#include <cmath>
+
 #include "kvo_index.h"
 
 namespace {
@@ -480,6 +483,8 @@ __global__ __launch_bounds__(512) void bwd_kvo_wide_kernel(
   constexpr int kRows = 64;                           // gathered (query, head) rows per pass
   constexpr int kDma = 4;                             // 1 KiB DMA pieces per wave and pass
   constexpr int KS = kHeadDim / 16;                   // k-steps of S and dP over the head dimension
+  // a raw score that any scale (not zero: run_backward) turns into weight zero
+  const float hidden = __uint_as_float((__float_as_uint(scale_log2) & 0x80000000u) ^ 0xFF800000u);
   __shared__ __align__(16) BwdWideSmem sm;
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
@@ -657,7 +662,7 @@ __global__ __launch_bounds__(512) void bwd_kvo_wide_kernel(
       if (__builtin_amdgcn_readfirstlane(sm.partial[buf]) != 0) {   // rows that do not see the whole block
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          acc_s[e] = key <= sm.rpos[buf][quad_row + 8 * (e >> 2) + (e & 3)] ? acc_s[e] : -INFINITY;
+          acc_s[e] = key <= sm.rpos[buf][quad_row + 8 * (e >> 2) + (e & 3)] ? acc_s[e] : hidden;
       }
       // P and dS in place, four rows (one quad of registers) at a time
       auto weights = [&](int g4) {
@@ -1031,7 +1036,10 @@ int run_backward(const void* q, const void* k, const void* v, const void* o, con
   const auto kvo = BK == 64 ? bwd_kvo_kernel : bwd_kvo_wide_kernel;
   constexpr int threads = BK == 64 ? kBwdThreads : 512;
   const int nctas = persistent_ctas(kvo, threads, &ctas);
-  const float sl2 = softmax_scale * kLog2e;
+  // the 128-key kernel masks raw scores, so it takes the smallest normal number
+  // for a zero scale (no exponent of scores below 2^100 moves by more than 2^-26)
+  float sl2 = softmax_scale * kLog2e;
+  if (BK == 128 && std::fabs(sl2) < FLT_MIN) sl2 = std::copysign(FLT_MIN, sl2);
   for (int64_t r0 = 0; r0 < seqs->total_q_rows; r0 += pl.chunk_rows) {
     const int64_t nr = std::min<int64_t>(pl.chunk_rows, seqs->total_q_rows - r0);
     build_reverse_index(block_ids, sq, blk_base, H_kv, BK, topk, pl.nbcap, pl.ntile, pl.nscan, r0, nr, cnt,

@@ -16,6 +16,7 @@ import torch
 
 import oracle.msa_oracle as O
 from paper_2606_13392_amd import msa, synth
+from tests.test_gpu_backward import _check_all, _setup
 from tests.util import check_outputs, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -85,3 +86,18 @@ def test_scale_forward(case, scale):
         outs["decode"] = call("decode")
     for kind, (o, lse) in outs.items():
         check_outputs(o[rows].float().cpu().numpy(), lse[rows].cpu().numpy(), o_ref, l_ref, f"{name} {kind}")
+
+
+@pytest.mark.parametrize("scale", SCALES)
+@pytest.mark.parametrize("bk", [64, 128])
+def test_scale_backward(bk, scale):
+    """Blocks partly visible to their rows: a row's own and a sequence's last."""
+    p, x, ids = _setup(f"scale_bwd_{bk}", [150, 70], [150, 333], 16, 2, 3, None, bk)
+    dev = torch.device("cuda")
+    seqs = msa.Seqs.from_problem(p, dev)
+    d = {n: to_dev(a) for n, a in x.items()}
+    ids_d = torch.from_numpy(ids).to(dev)
+    o, lse = msa.sparse_attn_decode(d["q"], d["k"], d["v"], ids_d, seqs, bk, softmax_scale=scale)
+    got = msa.sparse_attn_backward(d["q"], d["k"], d["v"], o, lse, d["d_o"], ids_d, seqs, bk, softmax_scale=scale)
+    ref = O.sparse_attention_backward(x["q"], x["k"], x["v"], x["d_o"], ids, O.layout_of(p), bk, scale=scale)
+    _check_all(f"scale_bwd_{bk}", [t.float().cpu().numpy() for t in got], ref)
