@@ -40,7 +40,9 @@
  *   Concurrent calls from several host threads are safe when they use
  *   distinct outputs and workspaces (msa_index_topk_noalloc calls on one GPU
  *   share its scratch array and must not overlap).
- * - NaN or Inf inputs give unspecified (but memory-safe) results.
+ * - NaN or Inf inputs give unspecified (but memory-safe) results.  In the sparse
+ *   forward calls they stay local: a row that does not list a key block is not
+ *   touched by what the block holds.
  *
  * Sequence layout (struct msa_seqs)
  * ---------------------------------

@@ -20,6 +20,11 @@
 // none per score).  (Skipping a block in the waves none of whose rows selected
 // it needs the score, softmax and value phases apart from one another: the
 // merged control flow spilled 65 - 130 registers.)  No partial leaves the CTA.
+// Weight zero hides finite keys and values only; a NaN or infinity in a block
+// would reach the rows that did not select it, always as a NaN in their sum or
+// output.  A tile that ends with one walks its blocks again, one at a time,
+// with a selection per row in place of the zero weights (the same results to
+// the bit where the inputs are finite).
 //
 // CTAs are ordered group-fastest: consecutive CTAs go to different XCDs, so
 // each XCD's L2 holds the K / V of its own groups, and every group's longest
@@ -68,6 +73,7 @@ struct Visits {
   uint32_t at[kMaxBlocks * SUB];         // per visited sub-block: its first key row / 64 (paged: in the pool)
   uint16_t sub[kMaxBlocks * SUB];        // ... and its index in the sequence
   int32_t n;
+  int32_t redo;                          // some row's result is not finite
 };
 struct NoVisits {};
 
@@ -240,7 +246,10 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
         if (SUB == 2) tail = tail || __ballot(any != 0 && (b * SUB + 1) * kSub > p_last) != 0;
         cnt += __popcll(m);
       }
-      if (lane == 0) vis.n = cnt * SUB - (tail ? 1 : 0);
+      if (lane == 0) {
+        vis.n = cnt * SUB - (tail ? 1 : 0);
+        vis.redo = 0;
+      }
     }
     __syncthreads();
     nvisit = vis.n;
@@ -405,7 +414,10 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc_s[i][e] = exp2_hw(fmaf(acc_s[i][e], scale_log2, neg));
+      for (int e = 0; e < 16; ++e) {
+        const float w = exp2_hw(fmaf(acc_s[i][e], scale_log2, neg));
+        acc_s[i][e] = !SPARSE || sel ? w : 0.f;
+      }
     float lsum = 0.f;
 #pragma unroll
     for (int u = 0; u < kSub / 16; ++u) {
@@ -431,18 +443,18 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
       for (int i = 0; i < kDim / 32; ++i) acc_o[i] *= alpha_pend;
     }
   };
-  // O^T += V^T P^T from one value sub-block (A operand read down V's columns)
-  // in 16 fenced MFMA slots, beside(j) after the j-th
+  // V^T operand of k-step u, dim tile td, read down V's columns
+  auto read_vt = [&](const uint16_t* vbuf, int u, int td) -> bf16x8 {
+    const char* a0 = reinterpret_cast<const char*>(vbuf) + lo.vs[td] + 2 * (32 * (u >> 1) + 16 * (u & 1)) * kDim;
+    const uint2 x0 = lds_tr4(reinterpret_cast<const uint16_t*>(a0));
+    const uint2 x1 = lds_tr4(reinterpret_cast<const uint16_t*>(a0 + 2 * 8 * kDim));  // rows +8: same permutation
+    return __builtin_bit_cast(bf16x8, make_uint4(x0.x, x0.y, x1.x, x1.y));
+  };
+  // O^T += V^T P^T from one value sub-block in 16 fenced MFMA slots, beside(j)
+  // after the j-th
   auto pv = [&](const uint16_t* vbuf, auto beside) {
-    const char* vbb = reinterpret_cast<const char*>(vbuf);
     constexpr int NO = (kSub / 16) * (kDim / 32);
-    auto vread = [&](int j) -> bf16x8 {
-      const int u = j / (kDim / 32), td = j % (kDim / 32);
-      const char* a0 = vbb + lo.vs[td] + 2 * (32 * (u >> 1) + 16 * (u & 1)) * kDim;
-      const uint2 x0 = lds_tr4(reinterpret_cast<const uint16_t*>(a0));
-      const uint2 x1 = lds_tr4(reinterpret_cast<const uint16_t*>(a0 + 2 * 8 * kDim));  // rows +8: same permutation
-      return __builtin_bit_cast(bf16x8, make_uint4(x0.x, x0.y, x1.x, x1.y));
-    };
+    auto vread = [&](int j) { return read_vt(vbuf, j / (kDim / 32), j % (kDim / 32)); };
     bf16x8 vr[NO];
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) vr[j] = vread(j);
@@ -577,6 +589,50 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
     __syncthreads();
     rescale();
     pv(ring.v[b & 1], nothing);
+
+    if constexpr (SPARSE) {
+      float zero = l_run * 0.f;             // NaN unless everything is finite
+#pragma unroll
+      for (int i = 0; i < kDim / 32; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) zero = fmaf(acc_o[i][e], 0.f, zero);
+      if (__ballot(zero != 0.f) && lane == 0) vis.redo = 1;
+      __syncthreads();
+      if (vis.redo != 0) {                  // uniform over the CTA
+#pragma unroll
+        for (int i = 0; i < kDim / 32; ++i) acc_o[i] = f32x16{};
+        m_run = -INFINITY;
+        l_run = 0.f;
+#pragma unroll 1
+        for (int i = 0; i < nvisit; ++i) {
+          const int at = place(i), sub = index(i);
+          const bool sel = (rows_of(sub) >> jq) & 1u;
+          __syncthreads();                  // the previous sub-block's readers are done
+          if constexpr (kDma) {
+            dma(kb, lo.kg, false, at, sub, ring.k[0]);
+            dma(vb, lo.vg, true, at, sub, ring.v[0]);
+          } else {
+            fetch(kb, at, sub, rk);
+            store(rk, false, ring.k[0]);
+            fetch(vb, at, sub, rk);
+            store(rk, true, ring.v[0]);
+          }
+          __builtin_amdgcn_s_waitcnt(0);
+          __syncthreads();
+          f32x16 acc_s[MT];
+          scores(ring.k[0], acc_s);
+          const float alpha = softmax(acc_s, sub * kSub, sel, std::true_type{});
+#pragma unroll
+          for (int td = 0; td < kDim / 32; ++td) {
+            f32x16 d = acc_o[td] * alpha;
+#pragma unroll
+            for (int u = 0; u < kSub / 16; ++u) d = mfma32x32x16(read_vt(ring.v[0], u, td), bp[u], d);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc_o[td][e] = sel ? d[e] : acc_o[td][e];
+          }
+        }
+      }
+    }
   }
 
   if (!valid) return;
