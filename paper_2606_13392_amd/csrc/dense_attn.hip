@@ -63,7 +63,8 @@ extern "C" int msa_dense_attn(const void* q, const void* k, const void* v, const
   const int G = num_q_heads / num_kv_heads;
   const int qt = kWaves * (32 / G);
   int64_t tiles;
-  const flash::Grid gr = flash::plan_grid(seqs, qt, seqs->max_q_rows, &tiles);
+  flash::Grid gr = flash::plan_grid(seqs, qt, seqs->max_q_rows, &tiles);
+  gr.tile_fast = flash::tile_fast(seqs, num_kv_heads, qt);
   if (tiles * num_kv_heads >= (int64_t(1) << 31)) return MSA_ERR_UNSUPPORTED;
   const auto kernel = flash::flash_tile_kernel<uint16_t, 64, false, false, kWaves>;
   msa_prof::launch("dense_prefill_kernel", kernel, dim3(static_cast<unsigned>(tiles * num_kv_heads)),

@@ -28,7 +28,8 @@
 //
 // CTAs are ordered group-fastest: consecutive CTAs go to different XCDs, so
 // each XCD's L2 holds the K / V of its own groups, and every group's longest
-// tiles start first.
+// tiles start first.  The dense call orders them tile-fastest where a
+// sequence's K and V outgrow the last-level cache (Grid, kCacheBytes).
 #pragma once
 
 #include <algorithm>
@@ -118,11 +119,29 @@ struct LaneOffsets {
 // has no tiles past max_rows.
 struct Grid {
   int32_t tiles;
+  bool tile_fast;                        // dense: all tiles of a group, then the next group's
 };
+// A dense sequence with more K and V than the last-level cache (256 MiB) runs
+// one group at a time: all CTAs stream the same K and V, which then come from
+// that cache for all XCDs but the first to ask.  Group-fastest every XCD is the
+// first to ask for its own group's.  A prompt, whose tiles differ in length,
+// does so only with many tiles per group (kManyTiles): the last group's longest
+// tile starts late.  Group-fastest against tile-fastest on MI355X, heads on
+// groups: 64 on 8 (4 KiB per key), prompts of 32768 keys 15.7 / 16.0 ms, 49152
+// 35.3 / 35.5, 65536 63.1 / 62.7, 131072 257 / 249; 8192 rows on 1M keys 258 /
+// 246; 12 sequences of 3000 keys 1.68 / 1.81.  Prompts, 16 on 16, 32768 keys
+// (128 tiles) 4.3 / 5.1, 98304 (384) 38.0 / 37.9; 64 on 16, 32768 (512) 16.4 /
+// 16.7, 65536 (1024) 67.4 / 65.4.  8192 rows on 64K keys, 32 on 32: 9.3 / 9.1.
+constexpr int64_t kCacheBytes = int64_t(1) << 28;
+constexpr int64_t kManyTiles = 1024;
+inline bool tile_fast(const msa_seqs* seqs, int H_kv, int qt) {
+  const int64_t keys = seqs->max_kv_len, rows = seqs->max_q_rows;
+  return keys * H_kv * (2 * kDim * 2) >= kCacheBytes && (2 * rows <= keys || rows >= kManyTiles * qt);
+}
 inline Grid plan_grid(const msa_seqs* seqs, int qt, int64_t max_rows, int64_t* tiles) {
   *tiles = seqs->num_seqs == 1 ? (std::min<int64_t>(seqs->max_q_rows, max_rows) + qt - 1) / qt
                                : seqs->total_q_rows / qt + seqs->num_seqs;
-  return Grid{static_cast<int32_t>(std::min<int64_t>(*tiles, 0x7FFFFFFF))};
+  return Grid{static_cast<int32_t>(std::min<int64_t>(*tiles, 0x7FFFFFFF)), false};
 }
 // Sequence and tile of grid tile `u` (wave-uniform).
 __device__ __forceinline__ void locate_tile(const msa_seqs& sq, const Grid& gr, int u, int qt, int* seq, int* tile) {
@@ -183,9 +202,12 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
   const int qpw = 32 / G;                  // query rows per wave
   const int qt = WAVES * qpw;              // query rows per CTA
   const int jq = n / G, hh = n % G;
-  const int r = static_cast<int>(blockIdx.x % static_cast<unsigned>(H_kv));
+  const bool by_tile = !SPARSE && gr.tile_fast;
+  const unsigned inner = by_tile ? static_cast<unsigned>(gr.tiles) : static_cast<unsigned>(H_kv);
+  const int fast = static_cast<int>(blockIdx.x % inner), slow = static_cast<int>(blockIdx.x / inner);
+  const int r = by_tile ? slow : fast;
   int s, tile;
-  locate_tile(sq, gr, static_cast<int>(blockIdx.x / static_cast<unsigned>(H_kv)), qt, &s, &tile);
+  locate_tile(sq, gr, by_tile ? fast : slow, qt, &s, &tile);
   const SeqGeom g = seq_geom(sq, s);
   const int t0 = tile * qt;
   const int base_p = g.kv_len - g.q_rows;  // position of the sequence's first query row
@@ -477,7 +499,10 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
     constexpr bool masked = decltype(masked_t)::value;
     __builtin_amdgcn_s_waitcnt(0);        // this thread's copies of K_{b+1} and V_b have landed
     __syncthreads();                      // everyone's have, and block b-1's readers are done
-    if constexpr (kDma) {
+    if constexpr (!SPARSE) {              // sub-block i is at key 64 i: nothing carried from step to step
+      if (b + 2 < nvisit) dma(kb, lo.kg, false, b + 2, b + 2, ring.k[b & 1]);
+      dma(vb, lo.vg, true, b + 1, b + 1, ring.v[(b + 1) & 1]);
+    } else if constexpr (kDma) {
       if (b + 2 < nvisit) dma(kb, lo.kg, false, at2, sub2, ring.k[b & 1]);
       dma(vb, lo.vg, true, at1, sub1, ring.v[(b + 1) & 1]);
     } else {
@@ -486,12 +511,14 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
       if (b + 3 < nvisit) fetch(kb, at3, sub3, rk);
       if (b + 2 < nvisit) fetch(vb, at2, sub2, rv);
     }
-    const int key0 = sub1 * kSub;
+    const int key0 = (SPARSE ? sub1 : b + 1) * kSub;
     const bool sel = !SPARSE || ((word1 >> jq) & 1u);
-    at1 = at2; sub1 = sub2; at2 = at3; sub2 = sub3;
-    at3 = place(b + 4);
-    sub3 = index(b + 4);
-    word1 = rows_of(sub1);
+    if constexpr (SPARSE) {
+      at1 = at2; sub1 = sub2; at2 = at3; sub2 = sub3;
+      at3 = place(b + 4);
+      sub3 = index(b + 4);
+      word1 = rows_of(sub1);
+    }
     rescale();
     __builtin_amdgcn_sched_barrier(0);
     f32x16 acc_s[MT];
@@ -583,7 +610,11 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
       alpha_pend = sub0 < nfree ? softmax(acc_s, 0, sel, std::false_type{}) : softmax(acc_s, sub0 * kSub, sel, std::true_type{});
     }
     int b = 0;
-    for (; b + 1 < nvisit && sub1 < nfree; ++b) step(b, std::false_type{});
+    if constexpr (SPARSE) {
+      for (; b + 1 < nvisit && sub1 < nfree; ++b) step(b, std::false_type{});
+    } else {
+      for (; b + 1 < min(nfree, nvisit); ++b) step(b, std::false_type{});
+    }
     for (; b + 1 < nvisit; ++b) step(b, std::true_type{});
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();

@@ -98,3 +98,18 @@ def test_dense_workload_sampled(name, n_rows):
     o_ref, l_ref = _dense_rows_ref(p, d, rows)
     stats = check_outputs(o.float().cpu().numpy()[rows], l.cpu().numpy()[rows], o_ref, l_ref, name)
     _say(f"  O max-abs {stats[0]:.2e} rel-L2 {stats[1]:.2e} lse {stats[2]:.2e} over {len(rows)} rows")
+
+
+@pytest.mark.parametrize("keys", [8191, 8192])
+def test_dense_cta_orders(keys):
+    """64 groups: at 8192 keys a sequence's K and V reach the size from which
+    CTAs run one group's tiles after the other instead of all groups' at once."""
+    p = synth.packed_problem(f"dense_order_{keys}", [300, 0, 41], [keys, 5, 700], num_q_heads=64, num_kv_heads=64, topk=1,
+                             seed=keys)
+    x = {k: v for k, v in synth.generate_numpy(p).items() if k in ("q", "k", "v")}
+    seqs = msa.Seqs.from_problem(p, torch.device("cuda"))
+    o, l = msa.dense_attn(to_dev(x["q"]), to_dev(x["k"]), to_dev(x["v"]), seqs)
+    rows = [0, 127, 128, 299, 300, 340]
+    o_ref, l_ref = O.dense_causal_attention(x["q"], x["k"], x["v"], O.layout_of(p), rows=rows)
+    assert bool(torch.isfinite(o.float()).all()) and bool(torch.isfinite(l).all())
+    check_outputs(o[rows].float().cpu().numpy(), l[rows].cpu().numpy(), o_ref, l_ref, p.name)
