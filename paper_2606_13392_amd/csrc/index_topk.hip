@@ -1328,7 +1328,10 @@ constexpr int64_t kSplitTopkRows = 4096;                 // fewer index rows: no
 // (index_topk_rows_kernel); fewer rows or a larger k, one wave in a CTA of its own
 // up to one round, 16 waves per row beyond (index_topk_split_kernel).  Scores and
 // Top-k of one row of 8 groups of 64-key blocks, one wave against 16: 7.7 and 11 us
-// at 8K, 12 and 15 at 130K (2032 blocks), k 16; 30 and 24 at 520K, k 24 and 48.
+// at 8K, 12 and 15 at 130K (2032 blocks), k 16; 30 and 24 at 520K, k 24 and 48; 64
+// rows of 8 groups at 130K, k 64, 198 and 208; 160 rows at 6K, k 64, 17 and 48.  Over
+// 1 - 500 sequences of 1 - 4 rows, 1 - 8 groups, 100 - 2040 blocks and k 16 (below
+// 64 rows), 48 and 64, 530 calls, one wave took 0.35 - 1.00 of 16 waves' time.
 constexpr int kRowTopkMaxK = 33;
 constexpr int64_t kRowTopkMinRows = 64;
 constexpr int kRowTopkMaxBlocks = 4 * 2048;
@@ -1338,20 +1341,34 @@ constexpr int kOneWaveMaxBlocks = 2048;
 template <int D, int B>
 constexpr int kNarrowDepth = D == 64 ? 4 : 2;
 
-// Narrow kernel: up to three rounds of slices (of the 2048 waves the chip holds
-// with d_idx 128), waves take pieces of 4 blocks in CTAs of their own: the few
-// waves' chains of rounds are the time of small calls, and CTAs of one wave
-// spread evenly over the CUs and leave no long last round.  With their Top-k,
-// slices in CTAs of four against pieces in CTAs of one: d_idx 128, 128-key
-// blocks, one row at 8K 20.4 and 10.4 us, 36 rows at 65K 144 and 114, 64 rows of
-// 48K to 131K 244 and 242; d_idx 64, 64-key blocks, one row at 8K 10.3 and 7.7.
-// Longer calls stream the same with less setup in slices (64 rows at 131K, d_idx
-// 64: 196 and 208 us).  (The worst place found for pieces: 17 rows at 32K, d_idx
-// 128, read from the last-level cache, 28.7 and 32.7.)
-constexpr int64_t kNarrowPieceMaxSlices = 3 * 2048;
+// Narrow kernel: a wave scores a slice of 8 blocks, four to a CTA, or a piece of
+// 4 in a CTA of its own.  Pieces halve the wave's chain of rounds, which is the
+// time of small calls, and spread evenly over the CUs; slices stream the same
+// with less setup.  With 64-wide indexes pieces win or tie up to five rounds of
+// slice CTAs.  With 128-wide ones, whose waves hold half as many per CU, only
+// where the slice CTAs would fill less than half of the CUs or one whole round,
+// or leave a last round that fills less than half.  Scores and Top-k, slices
+// against pieces in us, keys read from memory (from the last-level cache):
+//   d_idx 128, 128-key blocks, rows x keys [slice CTAs]:  1 x 13K [4] 31 / 15
+//   (21 / 11), 8 x 51K [104] 38.9 / 36.7 (24.5 / 24.5), 40 x 13K [160] 44.6 / 47.3
+//   (27.9 / 31.9), 16 x 51K [208] 61.5 / 63.0 (40.3 / 41.1), 64 x 13K [256] 64.3 /
+//   60.3 (45.2 / 40.6), 17 x 65K [272] 90.9 / 82.8, 8 x 192K [376] 103.6 / 99.4
+//   (82.5 / 78.6), 32 x 51K [416] 106.1 / 106.4 (79.9 / 83.7), 128 x 13K [512]
+//   107.0 / 107.2 (79.4 / 84.7), 40 x 51K [520] 142.9 / 128.9 (110 / 101), 64 x 51K
+//   [832] 192 / 183 (161 / 152), 32 x 192K [1504] 301 / 303 (266 / 273);
+//   d_idx 64, 64-key blocks:  1 x 6K [4] 14.6 / 11.1 (11.1 / 8.3), 40 x 6K [160] 20.9
+//   / 21.2 (15.8 / 14.0), 17 x 33K [272] 30.8 / 28.1, 32 x 26K [416] 35.4 / 37.0 (26.1 /
+//   27.0), 128 x 6K [512] 36.2 / 37.2 (28.0 / 26.1), 200 x 6K [800] 51.2 / 48.9 (40.0 /
+//   34.3), 64 x 26K [832] 61.7 / 60.3 (41.5 / 40.4), 32 x 96K [1504] 95.0 / 97.7 (78.4 / 80.2).
+constexpr int64_t kCus = 256;
 constexpr int kNarrowPieceBlocks = 4;
-bool narrow_pieces(const IndexPlan& pl, int64_t units) {
-  return pl.narrow && units * ((pl.bcap + kSliceBlocks - 1) / kSliceBlocks) < kNarrowPieceMaxSlices;
+bool narrow_pieces(const IndexPlan& pl, int d_idx, int64_t units) {
+  const int64_t slices = (pl.bcap + kSliceBlocks - 1) / kSliceBlocks;
+  const int64_t ctas = units * ((slices + kWaves - 1) / kWaves);
+  if (!pl.narrow) return false;
+  if (d_idx == 64) return ctas < 5 * kCus;
+  const bool one_round = ctas > kCus - kCus / 8 && ctas <= kCus;
+  return ctas < 5 * kCus && ((ctas - 1) % kCus < kCus / 2 || one_round);
 }
 
 template <int D, int B, bool PAGED>
@@ -1370,7 +1387,7 @@ void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const 
     msa_prof::launch("index_block_max_lds_kernel", (index_block_max_lds_kernel<D, B, 64, PAGED>), grid, dim3(256), 0,
                      stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, cta_blocks, M, static_cast<int64_t>(pl.bcap), CM,
                      cm_stride, PM);
-  else if (narrow_pieces(pl, u1 - u0))
+  else if (narrow_pieces(pl, D, u1 - u0))
     msa_prof::launch("index_block_max_narrow_kernel",
                      (index_block_max_narrow_kernel<D, B, kNarrowDepth<D, B>, kNarrowPieceBlocks, 1, PAGED>), grid,
                      dim3(kWave), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
@@ -1438,7 +1455,7 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
     const unsigned ny = static_cast<unsigned>((pl.bcap + cta_blocks - 1) / cta_blocks);
     float* cm = cta_blocks == kBlocksPerCta ? CM : nullptr;
     // per-wave kernels: slices (or pieces) of consecutive blocks, one per wave
-    const bool pieces = narrow_pieces(pl, u1 - u0);
+    const bool pieces = narrow_pieces(pl, d_idx, u1 - u0);
     const int wave_blocks = pieces ? kNarrowPieceBlocks : kSliceBlocks;
     const int cta_waves = pieces ? 1 : kWaves;
     const int nslice = (pl.bcap + wave_blocks - 1) / wave_blocks;
