@@ -370,7 +370,9 @@ int msa_sparse_kl_backward(const void* index_q, const void* index_k, const void*
  *
  * While enabled, every kernel a call launches is bracketed by a pair of HIP
  * events recorded on the call's stream, filed under the kernel's name (e.g.
- * "kvo_attn_kernel", "index_block_max_lds_kernel").  The events are created
+ * "kvo_attn_kernel", "index_block_max_lds_kernel"; all variants of a template
+ * under one name, the query-tile attention kernel under "dense_prefill_kernel"
+ * or "tile_attn_kernel" by the call that runs it).  The events are created
  * on first use and kept for reuse (global state of the timer alone).
  *
  *   msa_profile_enable(on)   on != 0 starts recording for later calls, 0 stops.

@@ -1063,18 +1063,17 @@ __global__ __launch_bounds__(256) void index_topk_kernel(
   finish_row(list, topk - 1, t.lb, topk, t.out);
 }
 
-// kSplitWaves waves per index row (few long rows with a large k): each takes the
-// best of a consecutive share of the row; the sorted lists are merged pairwise
-// through LDS in log2(kSplitWaves) steps.
-constexpr int kSplitWaves = 16;
-
-__global__ __launch_bounds__(64 * kSplitWaves) void index_topk_split_kernel(
+// WAVES waves per index row, one row per CTA: each wave takes the best of a
+// consecutive share of the row in rounds of RP values per lane; the sorted lists
+// are merged pairwise through LDS in log2(WAVES) steps.  One wave takes the row
+// whole: fewer rows than the chip has SIMDs each get one to themselves.
+template <int WAVES, int RP>
+__global__ __launch_bounds__(WAVES * kWave) void index_topk_split_kernel(
     const float* __restrict__ M, int64_t ldm, msa_seqs sq, int unit_shift, int H_kv,
     int qr, int U, int rpu, int64_t u0, int64_t u1, int BK, int topk, int32_t* __restrict__ block_ids) {
-  __shared__ uint64_t lists[kSplitWaves][kWave];
-  __shared__ uint64_t s_buf[kSplitWaves][2 * kWave];
+  __shared__ uint64_t s_buf[WAVES][2 * kWave];
   const int lane = lane_id();
-  const int w = threadIdx.x / kWave;
+  const int w = WAVES == 1 ? 0 : threadIdx.x / kWave;
   const int64_t task = blockIdx.x;
   if (task >= (u1 - u0) * rpu) return;              // uniform over the CTA
   const RowTask t = locate_row(M, ldm, sq, unit_shift, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
@@ -1085,25 +1084,30 @@ __global__ __launch_bounds__(64 * kSplitWaves) void index_topk_split_kernel(
   }
   const int K1 = topk - 1;
   const float* mrow = t.mrow;
-  const int seg = (t.nscan + 4 * kSplitWaves - 1) / (4 * kSplitWaves) * 4;     // float4 loads: whole quads
-  const int b0 = w * seg;
   uint64_t list = 0ull;
-  if (K1 > 0 && b0 < t.nscan) {
-    list = row_best_keys<true, 8>(mrow + b0, min(seg, t.nscan - b0), K1, s_buf[w]);
-    if (lane < K1 && list != 0ull) list -= b0;       // columns of the row: a key's low word falls as the column rises
-    else list = 0ull;
-  }
-  list = wave_sort_desc_u64(list);
-  lists[w][lane] = list;
-  // step s: wave w (a multiple of 2s) merges in wave w + s's list, written at
-  // the previous step; the barrier orders the steps
+  if constexpr (WAVES == 1) {
+    if (K1 > 0) list = row_best_keys<true, RP>(mrow, t.nscan, K1, s_buf[0]);
+  } else {
+    __shared__ uint64_t lists[WAVES][kWave];
+    const int seg = (t.nscan + 4 * WAVES - 1) / (4 * WAVES) * 4;     // float4 loads: whole quads
+    const int b0 = w * seg;
+    if (K1 > 0 && b0 < t.nscan) {
+      list = row_best_keys<true, RP>(mrow + b0, min(seg, t.nscan - b0), K1, s_buf[w]);
+      if (lane < K1 && list != 0ull) list -= b0;     // columns of the row: a key's low word falls as the column rises
+      else list = 0ull;
+    }
+    list = wave_sort_desc_u64(list);
+    lists[w][lane] = list;
+    // step s: wave w (a multiple of 2s) merges in wave w + s's list, written at
+    // the previous step; the barrier orders the steps
 #pragma unroll
-  for (int s = 1; s < kSplitWaves; s <<= 1) {
-    __syncthreads();
-    if ((w & (2 * s - 1)) == 0) {
-      const uint64_t rev = lists[w + s][kWave - 1 - lane];   // ascending: bitonic with `list`
-      list = wave_bitonic_merge_desc_u64(list > rev ? list : rev);
-      lists[w][lane] = list;
+    for (int s = 1; s < WAVES; s <<= 1) {
+      __syncthreads();
+      if ((w & (2 * s - 1)) == 0) {
+        const uint64_t rev = lists[w + s][kWave - 1 - lane];   // ascending: bitonic with `list`
+        list = wave_bitonic_merge_desc_u64(list > rev ? list : rev);
+        lists[w][lane] = list;
+      }
     }
   }
   if (w == 0) finish_row(list, K1, t.lb, topk, t.out);
@@ -1227,27 +1231,6 @@ __global__ __launch_bounds__(kRowWaves * kWave) void index_topk_rows_kernel(
   finish_row(list, K1, t.lb, topk, t.out);
 }
 
-// One wave per CTA and index row, RP values per lane and round: fewer rows than
-// the chip has SIMDs each get one to themselves.
-template <int RP>
-__global__ __launch_bounds__(kWave) void index_topk_one_wave_kernel(
-    const float* __restrict__ M, int64_t ldm, msa_seqs sq, int unit_shift, int H_kv, int qr,
-    int U, int rpu, int64_t u0, int64_t u1, int BK, int topk, int32_t* __restrict__ block_ids) {
-  __shared__ uint64_t s_buf[2 * kWave];
-  const int lane = lane_id();
-  const int64_t task = blockIdx.x;
-  if (task >= (u1 - u0) * rpu) return;
-  const RowTask t = locate_row(M, ldm, sq, unit_shift, H_kv, qr, U, rpu, u0, task, BK, topk, block_ids);
-  if (!t.ok) return;
-  if (t.no_position) {
-    if (lane < topk) t.out[lane] = -1;
-    return;
-  }
-  const int K1 = topk - 1;
-  const uint64_t list = K1 > 0 ? row_best_keys<true, RP>(t.mrow, t.nscan, K1, s_buf) : 0ull;
-  finish_row(list, K1, t.lb, topk, t.out);
-}
-
 // The min(n, K) best of n scores, n <= 2 kWave, from registers.
 __device__ __forceinline__ uint64_t short_row_best_keys(const float* __restrict__ srow, int n, int K, uint64_t* buf) {
   const int lane = lane_id();
@@ -1326,7 +1309,7 @@ constexpr int64_t kSplitTopkRows = 4096;                 // fewer index rows: no
 // rounds of 2048 blocks), numerous enough to spread and the Top-k small enough for
 // the lane-maximum bound to keep a round's candidates within the wave's buffer
 // (index_topk_rows_kernel); fewer rows or a larger k, one wave in a CTA of its own
-// up to one round, 16 waves per row beyond (index_topk_split_kernel).  Scores and
+// up to one round, 16 waves per row beyond (index_topk_split_kernel of 1 and 16 waves).  Scores and
 // Top-k of one row of 8 groups of 64-key blocks, one wave against 16: 7.7 and 11 us
 // at 8K, 12 and 15 at 130K (2032 blocks), k 16; 30 and 24 at 520K, k 24 and 48; 64
 // rows of 8 groups at 130K, k 64, 198 and 208; 160 rows at 6K, k 64, 17 and 48.  Over
@@ -1336,6 +1319,7 @@ constexpr int kRowTopkMaxK = 33;
 constexpr int64_t kRowTopkMinRows = 64;
 constexpr int kRowTopkMaxBlocks = 4 * 2048;
 constexpr int kOneWaveMaxBlocks = 2048;
+constexpr int kSplitWaves = 16;
 
 // 64-key sub-blocks in flight per wave of the narrow kernel: about 128 VGPRs of K_idx.
 template <int D, int B>
@@ -1480,17 +1464,15 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
                        dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), dim3(kRowWaves * kWave), 0,
                        stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0, u1,
                        block_size, topk, block_ids);
-    else if (rows <= kSplitTopkRows && pl.bcap <= kOneWaveMaxBlocks)
-      msa_prof::launch("index_topk_split_kernel",
-                       pl.bcap <= 8 * kWave    ? index_topk_one_wave_kernel<8>
-                       : pl.bcap <= 16 * kWave ? index_topk_one_wave_kernel<16>
-                                               : index_topk_one_wave_kernel<32>,
-                       dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, M, static_cast<int64_t>(pl.bcap), sq,
-                       unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0, u1, block_size, topk, block_ids);
     else if (rows <= kSplitTopkRows)
-      msa_prof::launch("index_topk_split_kernel", index_topk_split_kernel, dim3(static_cast<unsigned>(rows)),
-                       dim3(64 * kSplitWaves), 0, stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift,
-                       num_kv_heads, pl.qr, pl.U, rpu, u0, u1, block_size, topk, block_ids);
+      msa_prof::launch("index_topk_split_kernel",
+                       pl.bcap <= 8 * kWave           ? index_topk_split_kernel<1, 8>
+                       : pl.bcap <= 16 * kWave        ? index_topk_split_kernel<1, 16>
+                       : pl.bcap <= kOneWaveMaxBlocks ? index_topk_split_kernel<1, 32>
+                                                      : index_topk_split_kernel<kSplitWaves, 8>,
+                       dim3(static_cast<unsigned>(rows)), dim3(pl.bcap <= kOneWaveMaxBlocks ? kWave : kSplitWaves * kWave),
+                       0, stream, M, static_cast<int64_t>(pl.bcap), sq, unit_shift, num_kv_heads, pl.qr, pl.U, rpu, u0,
+                       u1, block_size, topk, block_ids);
     else
       msa_prof::launch("index_topk_kernel", index_topk_kernel, dim3(static_cast<unsigned>((rows + kWaves - 1) / kWaves)),
                        dim3(256), 0, stream, M, static_cast<int64_t>(pl.bcap), static_cast<const float*>(cm), cm_stride,

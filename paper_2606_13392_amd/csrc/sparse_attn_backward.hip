@@ -1044,7 +1044,7 @@ int run_backward(const void* q, const void* k, const void* v, const void* o, con
     const int64_t nr = std::min<int64_t>(pl.chunk_rows, seqs->total_q_rows - r0);
     build_reverse_index(block_ids, sq, blk_base, H_kv, BK, topk, pl.nbcap, pl.ntile, pl.nscan, r0, nr, cnt,
                         tile_off, item_off, blk_tot, tpos, handles, stream, true);
-    msa_prof::launch("bwd_kvo_kernel", kvo, dim3(nctas), dim3(threads), 0, stream,
+    msa_prof::launch(BK == 64 ? "bwd_kvo_kernel" : "bwd_kvo_wide_kernel", kvo, dim3(nctas), dim3(threads), 0, stream,
                      static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                      static_cast<const uint16_t*>(v), static_cast<const uint16_t*>(d_o), lse,
                      static_cast<const float*>(delta), sq, static_cast<const int64_t*>(blk_base),

@@ -7,6 +7,7 @@ from __future__ import annotations
 import pytest
 
 import oracle.msa_oracle as O
+from paper_2606_13392_amd import msa
 from tests.test_gpu_backward import _check_all, _gpu, _run, _setup  # noqa: F401  (_gpu: the module's fixture)
 
 pytestmark = pytest.mark.gpu
@@ -40,3 +41,16 @@ def test_backward_reproducible_list_lengths(rows):
     first, *rest = (list(_run(p, x, ids)) for _ in range(3))
     for r in rest:
         assert all((a == b).all() for a, b in zip(first, r))
+
+
+@pytest.mark.parametrize("bk,kernel", [(64, "bwd_kvo_kernel"), (128, "bwd_kvo_wide_kernel")])
+def test_backward_kernel_by_block_size(bk, kernel):
+    p, x, ids = _setup("bwd_names", [70], [70], 4, 2, 2, None, bk)
+    msa.profile_reset()
+    msa.profile_enable(True)
+    try:
+        list(_run(p, x, ids))
+    finally:
+        msa.profile_enable(False)
+    assert {n for n in msa.profile_read() if n.startswith("bwd_kvo")} == {kernel}
+    msa.profile_reset()

@@ -481,8 +481,9 @@ def test_index_exact_ties(case):
 # no repeats, the boundary cases of the kernel choice).  One wave per index
 # row takes a Top-k of at most 33 over at most 8192 blocks with >= 64 rows;
 # the all-equal rows overflow that wave's candidate buffer and are ranked
-# again through the key batch.  16 waves share each row otherwise (k 34 and
-# 64, fewer rows, longer rows).
+# again through the key batch.  Otherwise (k 34 and 64, fewer rows, longer
+# rows) the split kernel gives each row a CTA: one wave up to 2048 blocks, 16
+# waves beyond.
 DECODE_TIE_CASES = [                           # ..., the Top-k kernel the call must launch
     ("dec_ties_period7_k16", 64, 8192, 1, 16, 7, "rows"),
     ("dec_ties_period5_k32", 32, 65536 - 100, 2, 32, 5, "rows"),
@@ -492,6 +493,9 @@ DECODE_TIE_CASES = [                           # ..., the Top-k kernel the call 
     ("dec_split_k34_64rows", 32, 30000, 2, 34, -1, "split"),
     ("dec_split_k33_32rows", 16, 30000, 2, 33, -1, "split"),
     ("dec_rows_8192_blocks", 8, 8192 * 64, 8, 16, -1, "rows"),
+    ("dec_16_waves_k64_ties", 2, 2100 * 64, 2, 64, 3, "split"),
+    ("dec_16_waves_k17", 2, 2050 * 64 + 9, 4, 17, -1, "split"),
+    ("dec_16_waves_long_rows", 8, 8200 * 64, 8, 16, -1, "split"),
 ]
 
 
