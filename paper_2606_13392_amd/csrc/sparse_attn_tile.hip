@@ -50,11 +50,24 @@ constexpr int64_t kMinSplitCtas = 512;
 // 75 us): the scores past the reach, and what the longest tile (1.5 us per 64
 // keys) outlasts the rest.  64 heads, k 32, 9000 tokens: 1.35 ms against 1.61
 // split at 8192; 8 heads, k 8: 95 us against 105 at 4096 tokens, 137 against
-// 116 at 6000.
+// 116 at 6000.  Scores are counted as a prompt's, half of rows x positions;
+// chunks on cached contexts have up to twice as many, but their key-block-outer
+// rows cost more as well (each block has few): of 422 chunk calls past the reach
+// the full count would send 37 the other way, 12 of them up to 1.4 times faster
+// and 22 up to 1.7 times slower.
 constexpr double kOuterLaunchUs = 75.0;
-constexpr double kTileUsPerScore = 1.6e-5 / 64;       // per query head and (row, position)
+constexpr double kTileUsPerScore = 3.2e-5 / 64;       // per query head and (row, position)
 constexpr double kTileUsPerKey = 1.5 / 64;
 constexpr int64_t kMinMeanRows = 256;                 // ... for prompts: short runs of rows fill tiles poorly
+// Chunks of few tiles on long contexts: with a slot for every tile the longest
+// one is the call's time, and key-block-outer the launches and the rows (each
+// what a tile row at the reach costs) are less than that from some length on:
+// 700 rows on 6672 keys, 24 heads on 8 groups, k 32, 177 us in tiles and 128; 300
+// on 7072, 64 heads, 164 and 140; 8 x 300 on 7072, 8 heads on 2 groups, 175 and
+// 150.  (Of 2148 chunk calls of 256 rows and more per sequence, sequences of
+// equal and of mixed lengths, 12 remain 3 - 14 % slower in tiles than they were
+// key-block-outer only, most where 576 - 760 tiles make a thin second round.)
+constexpr int64_t kTileSlots = 512;
 
 template <typename T, int BK, bool PAGED>
 int launch_tiles(const void* q, const void* k, const void* v, const int32_t* block_ids, const msa_seqs* seqs,
@@ -77,20 +90,27 @@ int launch_tiles(const void* q, const void* k, const void* v, const int32_t* blo
 int msa_tile_positions(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk) {
   const int64_t reach = static_cast<int64_t>((BK == 64 ? kTileReach<64> : kTileReach<128>) * topk * BK);
   const int64_t most = static_cast<int64_t>(flash::kMaxBlocks) * BK;
-  const int64_t len = seqs->max_kv_len;
+  const int64_t len = seqs->max_kv_len, rows = seqs->total_q_rows, context = len - seqs->max_q_rows;
+  const int qt = kTileWaves * (32 / (H_q / H_kv));
   int64_t cut = std::min(reach, most);
-  if (len > reach && len <= most && seqs->total_q_rows >= kMinMeanRows * seqs->num_seqs) {
-    const double past = static_cast<double>(len - reach);
+  if (len <= most && rows >= kMinMeanRows * seqs->num_seqs) {
     const double per_score = kTileUsPerScore * H_q;
-    const double extra = per_score * seqs->num_seqs * std::min<double>(seqs->max_q_rows, past) * past;
-    const double tail = kTileUsPerKey * len - per_score * seqs->total_q_rows * len;
-    if (extra + std::max(tail, 0.0) < kOuterLaunchUs) cut = len;
+    if (len > reach) {
+      const double past = static_cast<double>(len - reach);
+      const double extra = per_score / 2 * seqs->num_seqs * std::min<double>(seqs->max_q_rows, past) * past;
+      const double tail = kTileUsPerKey * len - per_score / 2 * rows * len;
+      if (extra + std::max(tail, 0.0) < kOuterLaunchUs) cut = len;
+    }
+    const int64_t per_seq = (seqs->max_q_rows + qt - 1) / qt;
+    const bool one_round =
+        std::min(rows / qt + seqs->num_seqs, seqs->num_seqs * per_seq) * H_kv <= kTileSlots;
+    if (context > 0 && cut >= len && one_round && kTileUsPerKey * len > kOuterLaunchUs + per_score * rows * reach) return 0;
   }
   int64_t tiles;
-  flash::plan_grid(seqs, kTileWaves * (32 / (H_q / H_kv)), cut, &tiles);
+  flash::plan_grid(seqs, qt, cut, &tiles);
   const int64_t ctas = tiles * H_kv;
   if (ctas < kMinTileCtas || ctas >= (int64_t(1) << 31)) return 0;
-  if (cut < len && (ctas < kMinSplitCtas || 2 * (len - seqs->max_q_rows) > reach)) return 0;
+  if (cut < len && (ctas < kMinSplitCtas || 2 * context > reach)) return 0;
   return static_cast<int>(cut);
 }
 

@@ -116,3 +116,25 @@ def test_tiles(case):
     o_ref, l_ref = O.sparse_attention(x["q"], x["k"], x["v"], ids, O.layout_of(p), bk, rows=rows,
                                       fmt="e4m3" if fp8 else "bf16", input_scales=scales if fp8 else (1.0, 1.0, 1.0))
     check_outputs(o[rows].float().cpu().numpy(), lse[rows].cpu().numpy(), o_ref, l_ref, name)
+
+
+@pytest.mark.parametrize("keys,kernel", [(6555, "tile_attn_kernel"), (6556, "kvo_attn_kernel")])
+def test_chunk_of_few_tiles(keys, kernel):
+    """300 rows appended to a context within the reach (8192 positions): past a
+    length the longest tile alone takes more than the other path."""
+    p = synth.packed_problem(f"chunk_{keys}", [300], [keys], num_q_heads=64, num_kv_heads=8, topk=32, seed=keys)
+    x = synth.generate_numpy(p)
+    q, k, v, seqs = *(to_dev(x[n]) for n in "qkv"), msa.Seqs.from_problem(p, torch.device("cuda"))
+    ids = torch.from_numpy(synth.random_block_ids(p)).cuda()
+    msa.profile_reset()
+    msa.profile_enable(True)
+    try:
+        o, lse = msa.sparse_attn_prefill(q, k, v, ids, seqs, 64)
+        torch.cuda.synchronize()
+    finally:
+        msa.profile_enable(False)
+    assert {n for n in msa.profile_read() if n.endswith("attn_kernel")} == {kernel}
+    msa.profile_reset()
+    od, ld = msa.sparse_attn_decode(q, k, v, ids, seqs, 64)
+    assert float((lse - ld).abs().max()) <= 1e-4
+    assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
