@@ -116,14 +116,6 @@ __device__ __forceinline__ void bwd_dma4(const void* src, void* dst) {
                :: "v"(src), "s"(bwd_lds_addr(dst)) : "m0");
 }
 
-__device__ __forceinline__ uint16_t raw_elem(const u32x4& w, int j) {
-  return static_cast<uint16_t>(w[j >> 1] >> (16 * (j & 1)));
-}
-__device__ __forceinline__ bf16x8 lds_pair_bf16x8(const uint16_t* lo, const uint16_t* hi) {
-  const uint2 a = *reinterpret_cast<const uint2*>(lo), b = *reinterpret_cast<const uint2*>(hi);
-  return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
-}
-
 // D[row, head] = sum_d dO . O; 16 lanes per (row, head), 8 dims each.
 __global__ __launch_bounds__(256) void bwd_delta_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ d_o,
                                                         int64_t pairs, float* __restrict__ delta) {
