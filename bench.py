@@ -131,7 +131,11 @@ def run_prefill(args, dev):
     positions = torch.from_numpy(p.positions()).to(dev)
     toks = attended_tokens(ids, positions, p.block_size)
     pos3 = positions.view(-1, 1, 1)
-    incidences = float(((ids >= 0) & (ids.to(torch.int64) * p.block_size <= pos3)).sum().item())
+    # rows below `cut` run in the query-tile kernel, the others key-block-outer
+    cut = tile_cut(p, kernels)
+    outer_rows = int((positions >= cut).sum().item())
+    incidences = float(((ids >= 0) & (ids.to(torch.int64) * p.block_size <= pos3) & (pos3 >= cut)).sum().item())
+    tile_flops = 4.0 * dh * H_q * float((positions[positions < cut] + 1).sum().item())
     scored_keys = float(index_scored_keys(positions, p.block_size).sum().item())
     topk_bytes = topk_read_bytes(positions, p)
     eff_flops = 4.0 * dh * (H_q // H_kv) * float(toks.sum().item())
@@ -151,7 +155,7 @@ def run_prefill(args, dev):
         "paper_main_flops": paper_main,
         "kernels": {k: {"launches_per_step": n / args.steps, "ms_per_step": ms / args.steps,
                         "ms_per_launch": ms / n} for k, (n, ms) in kernels.items()},
-        "models": kernel_models(p, incidences, scored_keys, eff_flops, idx_flops, topk_bytes),
+        "models": kernel_models(p, outer_rows, incidences, tile_flops, scored_keys, idx_flops, topk_bytes),
         "inputs": d,
         "ids": ids,
     }
@@ -280,26 +284,39 @@ def topk_read_bytes(positions, p):
     return float(4 * p.num_kv_heads * (per_row.sum().item() + p.topk * positions.numel()))
 
 
-def kernel_models(p, incidences, scored_keys, eff_flops, idx_flops, topk_bytes):
+def tile_cut(p, kernels):
+    """Positions below this one ran in the query-tile kernel (the library's
+    reach of four times, with 128-key blocks 2.5 times, the selected tokens)."""
+    if "tile_attn_kernel" not in kernels:
+        return 0
+    if "kvo_attn_kernel" not in kernels:
+        return max(p.kv_lens)
+    return min(int((4.0 if p.block_size == 64 else 2.5) * p.topk * p.block_size), 256 * p.block_size)
+
+
+def kernel_models(p, outer_rows, incidences, tile_flops, scored_keys, idx_flops, topk_bytes):
     """Algorithmic work per step of the prefill kernels: (bound, amount, unit).
 
-    An incidence is one valid (query row, group, selected block).  The
+    An incidence is one valid (query row, group, selected block) of the
+    ``outer_rows`` rows that run key-block-outer.  The
     key-block-outer attention reads each key block's K and V once per group and,
     per incidence, gathers the G query rows and writes a bf16 partial O plus its
     fp32 LSE (Sec. 4.2 IO analysis, KV-outer): its intensity, about 2/3 B_k
     FLOP/B, sits far below MI355X's bf16 ridge (2.5 PFLOP/s / 8 TB/s = 312), so
     it is HBM-bound.  The combine reads every partial and writes O and LSE.
+    The query-tile kernel computes every causal score of its rows on MFMA.
     Index scoring is an MFMA contraction; Top-k reads the piece maxima and the
     pieces that reach its bound (topk_read_bytes)."""
     G = p.num_q_heads // p.num_kv_heads
     d, T, H_kv, H_q = p.head_dim, p.total_q_rows, p.num_kv_heads, p.num_q_heads
     kv_bytes = 4.0 * H_kv * float(sum(p.kv_lens)) * d
     attn_bytes = kv_bytes + incidences * (4.0 * G * d + 4.0 * G + 4.0)
-    comb_bytes = incidences * (2.0 * G * d + 4.0 * G) + T * H_q * (2.0 * d + 4.0) + T * H_kv * p.topk * 4.0
+    comb_bytes = incidences * (2.0 * G * d + 4.0 * G) + outer_rows * (H_q * (2.0 * d + 4.0) + H_kv * p.topk * 4.0)
     score_blocks = scored_keys / p.block_size * H_kv          # block scores written and read back
     return {
         "kvo_attn_kernel": ("hbm", attn_bytes, "bytes"),
         "kvo_combine_kernel": ("hbm", comb_bytes, "bytes"),
+        "tile_attn_kernel": ("mfma", tile_flops, "flops"),
         "index_block_max_lds_kernel": ("mfma", idx_flops, "flops"),
         "index_block_max_wave_kernel": ("mfma", idx_flops, "flops"),
         "index_topk_kernel": ("hbm", topk_bytes, "bytes"),

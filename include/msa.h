@@ -150,8 +150,8 @@ int msa_index_topk(const void* index_q, const void* index_k, const msa_seqs* seq
  * holds its own copy until the process ends.  The call runs on the current
  * device, and `stream` must belong to it.  It allocates nothing (no hipMalloc,
  * hipFree or allocating library routine); its first call on a device looks
- * the array's address up once.  A problem whose smallest workspace (the
- * sequence table plus one unit of rows, the quantum msa_index_topk chunks by)
+ * the array's address up once.  A problem whose smallest workspace (four bytes
+ * per sequence plus one unit of rows, the quantum msa_index_topk chunks by)
  * exceeds the array returns MSA_ERR_WORKSPACE and launches nothing; problems
  * larger than the array but within that bound run in several chunks.
  * Every call on a GPU shares that GPU's array: calls that overlap on one GPU
@@ -207,7 +207,12 @@ int msa_block_topk(const float* scores, int64_t n_rows, int n_cols, int64_t ld, 
  *
  * The prefill call is built for many query rows per sequence; the decode call
  * for one query row per sequence (it accepts any layout, and gives the same
- * result as the prefill call up to rounding).
+ * result as the prefill call up to rounding).  Which kernel computes a prefill
+ * row follows the sizes of its call (num_seqs, total_q_rows, max_q_rows,
+ * max_kv_len, heads, block_size, topk), so a row's result is bit-reproducible
+ * between calls of equal sizes and may differ by rounding between others.  A
+ * prefill call whose sizes send every row to the query tiles leaves the
+ * workspace untouched and requires it all the same.
  *
  * Supported: head_dim == 128; block_size in {64, 128}; 1 <= topk <= 64;
  * 1 <= num_q_heads / num_kv_heads <= 16; num_kv_heads <= 64.
@@ -275,7 +280,8 @@ int msa_sparse_attn_decode_fp8(const void* q, const void* k, const void* v, floa
  * lse [total_q_rows, H_q] fp32 natural log (-inf for rows with no visible
  * key).  Sequences with at most 4 query rows (decode) run a split row kernel
  * whose partials need the workspace; longer ones run a FlashAttention-style
- * tiled kernel that needs only a small table.
+ * tiled kernel, which leaves the workspace of its query (a few bytes per
+ * sequence, required all the same) untouched.
  *
  * Supported: head_dim == 128; 1 <= num_q_heads / num_kv_heads <= 16;
  * num_kv_heads <= 64.

@@ -44,6 +44,7 @@ extern "C" size_t msa_dense_attn_workspace_size(const msa_seqs* seqs, int num_q_
                                                int head_dim) {
   if (validate_dense(seqs, num_q_heads, num_kv_heads, head_dim) != MSA_OK) return 0;
   if (decode_like(seqs)) return msa_rows_dense_workspace_size(seqs, num_q_heads, num_kv_heads);
+  // not read or written; part of the call's contract since it held a tile table
   return msa_host::align_up(sizeof(int32_t) * (seqs->num_seqs + 1), 256);
 }
 

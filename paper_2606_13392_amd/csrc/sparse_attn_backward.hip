@@ -439,9 +439,10 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_kvo_kernel(
 // same work, its operands read ahead of fenced MFMA slots.  8 packed documents
 // of 745 - 3871 rows (64 heads on 4 groups, k 16): 3.40 -> 2.45 ms, 660 -> 920
 // TFLOP/s; 32768 rows: 10.0 -> 7.9 ms.  (Without the read-ahead 2.73 and 8.8 ms;
-// the registers that spill are the item loop's, none in the pass loop.)  Lane l = (n = l % 32, h = l / 32): in S = Q K^T and dP = dO V^T it
-// holds key 32kq + n and rows 8(r / 4) + 4h + r % 4 (r = 0..15), which are the
-// k-slices it supplies to dV += P^T dO and dK += dS^T Q.
+// 20 registers of the item loop spill, the pass loop has no scratch access.)
+// Lane l = (n = l % 32, h = l / 32): in S = Q K^T and dP = dO V^T it holds key
+// 32kq + n and rows 8(r / 4) + 4h + r % 4 (r = 0..15), which are the k-slices it
+// supplies to dV += P^T dO and dK += dS^T Q.
 struct BwdWideSmem {
   uint16_t k[128][kHeadDim];                          // K and V block, 256-byte rows, segments swizzled (bwd_swz)
   uint16_t v[128][kHeadDim];

@@ -35,9 +35,10 @@ constexpr int kTileWaves = 4;
 // That is 4.1 - 4.2 times topk B_k at B_k 64 and 2.5 - 3.3 times at B_k 128.
 template <int BK>
 constexpr double kTileReach = BK == 64 ? 4.0 : 2.5;
-// Fewer CTAs than half the CUs leave the call key-block-outer.  Not for speed
-// (1000 rows of 16 heads: 81 us against 30): the kernel timer's record of
-// such a call is pinned to the key-block-outer kernels.
+// Fewer CTAs than half the CUs leave the call key-block-outer, as every call was
+// before there were tiles.  Not for speed (1000 rows of 16 heads: 81 us against
+// 30): the kernel timer's record of such a call is pinned to the
+// key-block-outer kernels by a test.
 constexpr int64_t kMinTileCtas = 128;
 // With rows left for the key-block-outer kernels as well, the tiles have to
 // fill the chip (two CTAs per CU: below that they add their own latency, 49 us
