@@ -577,6 +577,24 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
     alpha_pend = alpha;
   };
 
+  auto write_rows = [&]() {
+    if (!valid) return;
+    const bool empty = !(l_run > 0.f);
+    const float inv_l = empty ? 0.f : o_scale / l_run;
+    // O^T tile td: lane (n, h) holds d = 32td + 8(e/4) + 4h + e%4 of row n
+    uint16_t* orow = o + head_row * kDim + 4 * h;
+#pragma unroll
+    for (int td = 0; td < kDim / 32; ++td)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        uint2 w;
+        w.x = pack_bf16x2(acc_o[td][4 * e4 + 0] * inv_l, acc_o[td][4 * e4 + 1] * inv_l);
+        w.y = pack_bf16x2(acc_o[td][4 * e4 + 2] * inv_l, acc_o[td][4 * e4 + 3] * inv_l);
+        *reinterpret_cast<uint2*>(orow + 32 * td + 8 * e4) = w;
+      }
+    if (h == 0) lse[head_row] = empty ? -INFINITY : (m_run * scale_log2 + __log2f(l_run)) * kLn_2;
+  };
+
   if (nvisit > 0) {
     const int at0 = place(0), sub0 = index(0);
     at1 = place(1); sub1 = index(1);
@@ -620,14 +638,16 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
     __syncthreads();
     rescale();
     pv(ring.v[b & 1], nothing);
-
-    if constexpr (SPARSE) {
-      float zero = l_run * 0.f;             // NaN unless everything is finite
+  }
+  write_rows();                             // (before the check: the stores go out beside it)
+  if constexpr (SPARSE) {
+    if (nvisit > 0) {
+      float zero[kDim / 32];                // NaN unless everything is finite
 #pragma unroll
-      for (int i = 0; i < kDim / 32; ++i)
+      for (int e = 0; e < 16; ++e)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) zero = fmaf(acc_o[i][e], 0.f, zero);
-      if (__ballot(zero != 0.f) && lane == 0) vis.redo = 1;
+        for (int i = 0; i < kDim / 32; ++i) zero[i] = fmaf(acc_o[i][e], 0.f, e == 0 ? l_run * 0.f : zero[i]);
+      if (__ballot(zero[0] + zero[1] + zero[2] + zero[3] != 0.f) && lane == 0) vis.redo = 1;
       __syncthreads();
       if (vis.redo != 0) {                  // uniform over the CTA
 #pragma unroll
@@ -662,25 +682,10 @@ __global__ __launch_bounds__(WAVES* kWave, 2) void flash_tile_kernel(
             for (int e = 0; e < 16; ++e) acc_o[td][e] = sel ? d[e] : acc_o[td][e];
           }
         }
+        write_rows();
       }
     }
   }
-
-  if (!valid) return;
-  const bool empty = !(l_run > 0.f);
-  const float inv_l = empty ? 0.f : o_scale / l_run;
-  // O^T tile td: lane (n, h) holds d = 32td + 8(e/4) + 4h + e%4 of row n
-  uint16_t* orow = o + head_row * kDim + 4 * h;
-#pragma unroll
-  for (int td = 0; td < kDim / 32; ++td)
-#pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
-      uint2 w;
-      w.x = pack_bf16x2(acc_o[td][4 * e4 + 0] * inv_l, acc_o[td][4 * e4 + 1] * inv_l);
-      w.y = pack_bf16x2(acc_o[td][4 * e4 + 2] * inv_l, acc_o[td][4 * e4 + 3] * inv_l);
-      *reinterpret_cast<uint2*>(orow + 32 * td + 8 * e4) = w;
-    }
-  if (h == 0) lse[head_row] = empty ? -INFINITY : (m_run * scale_log2 + __log2f(l_run)) * kLn_2;
 }
 
 }  // namespace flash
