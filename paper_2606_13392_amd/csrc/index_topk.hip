@@ -1174,7 +1174,7 @@ __device__ __forceinline__ uint64_t row_best_keys(const float* __restrict__ srow
 #pragma unroll
     for (int v = 0; v < RP; ++v) {
       const int c = col_of(v);
-      const bool take = x[v] >= tf && (full || c < n);
+      const bool take = !(x[v] < tf) && (full || c < n);   // a NaN score as well: it ranks by its bits
       const uint64_t m = __ballot(take);
       if (m == 0) continue;
       const int pos = cnt + lanes_below(m);

@@ -117,6 +117,23 @@ def test_block_topk_row_widths(k, ld_pad):
         assert np.array_equal(ids, O.row_topk(x, k)), f"{B} columns, k {k}"
 
 
+@pytest.mark.parametrize("k", [16, 64])
+def test_block_topk_nan_columns_are_kept(k):
+    """A NaN score ranks by its sign and bits (above +inf, or below -inf), in
+    rows of every width alike; no column is lost to it."""
+    for B in (k, k + 2, 128, 129, 300, 700, 1500, 4000):
+        rng = np.random.default_rng([B, k])
+        x = rng.standard_normal((12, B)).astype(np.float32)
+        x[2:4, rng.choice(B, 5, replace=False)] = INF
+        for row in range(1, 12):                        # 1, 3, ... NaNs of either sign, up to all columns
+            at = rng.choice(B, B if row == 11 else min(B, 2 * row - 1), replace=False)
+            x[row, at] = np.where(rng.random(at.size) < 0.5, np.float32("nan"), -np.float32("nan"))
+        u = x.view(np.uint32).astype(np.int64)
+        order = np.where(u >> 31, 0xFFFFFFFF - u, u + (1 << 31))      # no zeros among the scores
+        want = np.sort(np.argsort(-order, axis=1, kind="stable")[:, :k], axis=1)
+        assert np.array_equal(msa.block_topk(torch.from_numpy(x).to("cuda"), k).cpu().numpy(), want), f"{B} columns"
+
+
 # name, rows, keys, H_kv, block, topk, equal keys
 INDEX_CASES = [
     # few units: CTAs score 16-block pieces and write no slice maxima
