@@ -41,7 +41,16 @@ constexpr int kBlocksPerCta = 64;      // key blocks per CTA slice, LDS kernel
 // A unit holds 2^unit_shift query rows of one sequence; sequence s owns units
 // from q_offsets[s] / 2^unit_shift + s on, at least as many as it needs.  With
 // unit_shift < 0 (every sequence has at most one row group and U = 1) unit s
-// is sequence s.
+// is sequence s.  With kCompactUnits added the units are numbered without gaps,
+// which a wave finds out from up to kCompactSeqs lengths: for the few CTAs of
+// small U = 1 calls, whose empty units in between would put the working CTAs on
+// some XCDs and CUs and leave others idle (21 sequences of 1 - 7 rows, 16 groups,
+// 6K - 49K keys of 128-key blocks: 22 us without gaps, 36 with them).  For more
+// sequences the count costs as much as it saves (200 of 4 rows at 10K, 32 groups:
+// 42 us, 38 with gaps).
+constexpr int kCompactUnits = 64;
+constexpr int kCompactSeqs = 128;
+
 struct UnitRows {
   bool ok;
   int s;
@@ -57,6 +66,29 @@ __device__ __forceinline__ UnitRows locate_unit(const msa_seqs& sq, int unit_shi
     if (uidx >= sq.num_seqs) return r;
     r.s = static_cast<int>(uidx);
     r.t0 = 0;
+  } else if (unit_shift >= kCompactUnits) {
+    const int shift = unit_shift - kCompactUnits;
+    int before = 0;                            // units of the sequences before s0
+    for (int s0 = 0;; s0 += kWave) {
+      if (s0 >= sq.num_seqs) return r;
+      const int s = s0 + lane_id();
+      const int rows = s < sq.num_seqs ? sq.q_offsets[s + 1] - sq.q_offsets[s] : 0;
+      const int own = rows > 0 ? (rows + (1 << shift) - 1) >> shift : 0;
+      int upto = own;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int x = __shfl_up(upto, off);
+        if (lane_id() >= off) upto += x;
+      }
+      const uint64_t past = __ballot(uidx < before + upto);
+      if (past == 0) {
+        before += __shfl(upto, kWave - 1);
+        continue;
+      }
+      const int j = __ffsll(static_cast<unsigned long long>(past)) - 1;
+      r.s = __builtin_amdgcn_readfirstlane(s0 + j);
+      r.t0 = __builtin_amdgcn_readfirstlane(static_cast<int>(uidx - before - __shfl(upto - own, j)) << shift);
+      break;
+    }
   } else {
     int lo = 0, n = sq.num_seqs;               // the sequence lies in [lo, lo + n)
     while (n > 1) {
@@ -1355,6 +1387,20 @@ bool narrow_pieces(const IndexPlan& pl, int d_idx, int64_t units) {
   return ctas < 5 * kCus && ((ctas - 1) % kCus < kCus / 2 || one_round);
 }
 
+// Wave kernel: a CTA's operand loads take what its CU's address unit gives, so
+// two working CTAs on one CU take twice as long.  In a grid of up to two per CU
+// with empty ones among them (lengths differ) the dispatcher places them so while
+// other CUs idle: an LDS request above half of a CU's keeps them apart.  16
+// groups, 30 sequences of 4 rows and up to 40K keys, d_idx 64, 128-key blocks 35.7
+// -> 22.0 us; 57 of 4 rows, 32 groups, up to 5000 keys 32 -> 21.5.  With more CTAs
+// the second one per CU hides latency (64 sequences at 60K: 45 us, apart 50).
+// Whole-row loads (d_idx 64, 64-key blocks) share a CU well.
+constexpr size_t kHalfCuLds = 84 * 1024;
+size_t wave_spread_lds(const IndexPlan& pl, bool whole_rows, const msa_seqs& sq, dim3 grid) {
+  const int64_t units = std::min<int64_t>(grid.y, sq.total_q_rows / pl.qr + sq.num_seqs);   // the others are empty
+  return units * grid.x <= 2 * kCus && !whole_rows ? kHalfCuLds : 0;
+}
+
 template <int D, int B, bool PAGED>
 void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const uint16_t* iq, const uint16_t* ik,
                       const msa_seqs& sq, int unit_shift, int H_kv, int64_t u0, int64_t u1, int cta_blocks, float* M,
@@ -1382,8 +1428,8 @@ void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const 
                      dim3(kWaves * kWave), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
                      static_cast<int64_t>(pl.bcap));
   else
-    msa_prof::launch("index_block_max_wave_kernel", (index_block_max_wave_kernel<D, B, PAGED>), grid, dim3(256), 0,
-                     stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M, static_cast<int64_t>(pl.bcap));
+    msa_prof::launch("index_block_max_wave_kernel", (index_block_max_wave_kernel<D, B, PAGED>), grid, dim3(256),
+                     wave_spread_lds(pl, D == 64 && B == 64, sq, grid), stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M, static_cast<int64_t>(pl.bcap));
 }
 
 // A paged key side runs the kernels instantiated for it.
@@ -1419,7 +1465,8 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
   int64_t chunk = static_cast<int64_t>((workspace_bytes - pl.hdr_bytes) / pl.unit_bytes);
   if (chunk > pl.max_units) chunk = pl.max_units;
 
-  const int unit_shift = pl.seq_units ? -1 : __builtin_ctz(static_cast<unsigned>(pl.qr * pl.U));
+  int unit_shift = pl.seq_units ? -1 : __builtin_ctz(static_cast<unsigned>(pl.qr * pl.U));
+  if (pl.U == 1 && !pl.seq_units && seqs->num_seqs <= kCompactSeqs) unit_shift += kCompactUnits;
   float* M = reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.hdr_bytes);
   // chunk maxima CM[chunk][row] follow the chunk's score rows
   const int64_t cm_stride = chunk * pl.U * kWave;

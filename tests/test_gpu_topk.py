@@ -150,6 +150,12 @@ INDEX_CASES = [
     ("decode_16_waves", [1, 1], [2050 * 64, 2100 * 64 + 3], 4, 64, 17, False),
     ("decode_16_waves_ties", [1], [2200 * 64 + 3], 2, 64, 48, True),
     ("decode_wide_pieces", [1, 3, 1], [77 * 128 + 1, 128 * 9, 300], 4, 128, 12, False),
+    # wave kernel: one CTA per CU up to 512 of them, more beyond; units numbered without gaps up to 128 sequences
+    ("wave_one_cta_per_cu", [4, 1, 7, 4, 0, 3], [600 * 64 + 9, 64, 7, 100 * 64, 0, 1000], 32, 64, 16, False),
+    ("wave_wide_one_cta_per_cu", [4, 1, 7, 2], [70 * 128 + 9, 128, 7, 1000], 16, 128, 16, False),
+    ("units_of_128_sequences", [4, 1, 0, 3] * 32, [300, 64, 5, 200] * 32, 32, 64, 4, False),
+    ("units_of_129_sequences", [4, 1, 0, 3] * 32 + [4], [300, 64, 5, 200] * 32 + [900], 32, 64, 4, False),
+    ("wave_many_ctas", [4, 1, 7, 4] * 30, [300 * 64 + 9, 64, 7, 1000] * 30, 16, 64, 16, False),
     ("decode_many_units_slices", [1] * 200, [256 * 64 + 5] + [700] * 199, 8, 64, 8, False),
 ]
 
