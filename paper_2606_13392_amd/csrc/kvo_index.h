@@ -236,16 +236,28 @@ constexpr int kScanOne = 16384;       // 1024 threads x 16
 __global__ __launch_bounds__(1024) void kvo_scan_one_kernel(const int32_t* __restrict__ cnt, int n,
                                                             int32_t* __restrict__ tile_off,
                                                             int32_t* __restrict__ item_off) {
+  // A thread's counts (up to four quads) are requested together and stay in
+  // registers: read one after the other, 9520 tiles took 35 us, more than the
+  // three kernels (20).  A quad that starts below n ends inside the array.
+  constexpr int kQuads = kScanOne / 1024 / 4;
+  typedef __attribute__((__vector_size__(4 * sizeof(int32_t)))) int32_t i32x4;
   __shared__ int32_t wa[1024 / kWave], wb[1024 / kWave];
   const int t = threadIdx.x, lane = lane_id(), wave = t / kWave;
-  const int per = (n + 1023) / 1024;
-  const int i0 = min(n, t * per), i1 = min(n, i0 + per);
+  const int quads = (n + 4095) / 4096;                // per thread, uniform
+  const int i0 = 4 * quads * t;
+  i32x4 c[kQuads];
+#pragma unroll
+  for (int j = 0; j < kQuads; ++j)
+    c[j] = j < quads && i0 + 4 * j < n ? *reinterpret_cast<const i32x4*>(cnt + i0 + 4 * j) : i32x4{};
   int32_t ta = 0, tb = 0;
-  for (int i = i0; i < i1; ++i) {
-    const int32_t c = cnt[i];
-    ta += c;
-    tb += (c + kItemQueries - 1) / kItemQueries;
-  }
+#pragma unroll
+  for (int j = 0; j < kQuads; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      c[j][e] = i0 + 4 * j + e < n ? c[j][e] : 0;
+      ta += c[j][e];
+      tb += (c[j][e] + kItemQueries - 1) / kItemQueries;
+    }
   // sums of the threads before this one: within the wave, then over the waves
   int32_t a = ta, b = tb;
   for (int off = 1; off < kWave; off <<= 1) {
@@ -256,12 +268,26 @@ __global__ __launch_bounds__(1024) void kvo_scan_one_kernel(const int32_t* __res
   __syncthreads();
   int32_t pa = a - ta, pb = b - tb;
   for (int w = 0; w < wave; ++w) { pa += wa[w]; pb += wb[w]; }
-  for (int i = i0; i < i1; ++i) {
-    tile_off[i] = pa;
-    item_off[i] = pb;
-    const int32_t c = cnt[i];
-    pa += c;
-    pb += (c + kItemQueries - 1) / kItemQueries;
+#pragma unroll
+  for (int j = 0; j < kQuads; ++j) {
+    if (j >= quads) break;
+    i32x4 oa, ob;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      oa[e] = pa;
+      ob[e] = pb;
+      pa += c[j][e];
+      pb += (c[j][e] + kItemQueries - 1) / kItemQueries;
+    }
+    const int i = i0 + 4 * j;
+    if (i + 4 <= n) {
+      *reinterpret_cast<i32x4*>(tile_off + i) = oa;
+      *reinterpret_cast<i32x4*>(item_off + i) = ob;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (i + e < n) { tile_off[i + e] = oa[e]; item_off[i + e] = ob[e]; }
+    }
   }
   if (t == 1023) { tile_off[n] = pa; item_off[n] = pb; }
 }

@@ -138,3 +138,31 @@ def test_chunk_of_few_tiles(keys, kernel):
     od, ld = msa.sparse_attn_decode(q, k, v, ids, seqs, 64)
     assert float((lse - ld).abs().max()) <= 1e-4
     assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
+
+
+@pytest.mark.parametrize("blocks", [1, 1365, 1366, 5461, 5462])
+def test_reverse_index_scan_sizes(blocks):
+    """Three groups: 3, 4095 and 4098 tiles around one quad of counts a thread,
+    16383 and 16386 around the one-CTA scan's limit."""
+    rows, keys = 40, 64 * blocks
+    rows = min(rows, keys)
+    g = torch.Generator(device="cuda").manual_seed(blocks)
+    q, k, v = (torch.randn((n, 3, 128), dtype=torch.bfloat16, device="cuda", generator=g) for n in (rows, keys, keys))
+    seqs = msa.Seqs([rows], [keys], [0], keys, torch.device("cuda"))
+    local = (torch.arange(keys - rows, keys, device="cuda") // 64).view(-1, 1, 1)
+    ids = (torch.rand((rows, 3, 8), device="cuda", generator=g) * local).int()       # may repeat, below the local block
+    ids = torch.where((ids[..., :, None] == ids[..., None, :]).tril(-1).any(-1), -1, ids)
+    ids[..., :1] = local.int()
+    ids = torch.where((torch.arange(8, device="cuda") > 0) & (ids == local), -1, ids).int().contiguous()
+    msa.profile_reset()
+    msa.profile_enable(True)
+    try:
+        o, lse = msa.sparse_attn_prefill(q, k, v, ids, seqs, 64)
+        torch.cuda.synchronize()
+    finally:
+        msa.profile_enable(False)
+    assert ("kvo_scan_one_kernel" in msa.profile_read()) == (3 * blocks <= 16384)
+    msa.profile_reset()
+    od, ld = msa.sparse_attn_decode(q, k, v, ids, seqs, 64)
+    assert float((lse - ld).abs().max()) <= 1e-4
+    assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
