@@ -87,15 +87,16 @@ __device__ __forceinline__ void store_v_transposed(AttnSmem& sm, const R (&raw_i
 // T: element type of Q, K and V (uint16_t = bf16 bits, uint8_t = e4m3 bits);
 // o_scale multiplies O (the V dequantisation scale for e4m3).
 // A row's slots are topk << sub_shift: slot s is keys 64 (s % 2^sub_shift) ..
-// of its block id s >> sub_shift.
+// of its block id s >> sub_shift.  A wave takes slots_per_wave consecutive ones,
+// or with slot_step > 1 every slot_step-th (the number of waves).
 template <typename T, bool PAGED>
 // two CTAs per CU in 256 registers: bf16 on a contiguous cache 108 -> 106 us
 // per 128K step against one wave per SIMD
 __global__ __launch_bounds__(64 * kAttnWaves, 2) void attn_rows_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ block_ids, msa_seqs sq, int H_q, int H_kv, int topk,
-    int sub_shift, int slots_per_wave, float scale_log2, float o_scale, uint16_t* __restrict__ o, float* __restrict__ lse,
-    float* __restrict__ o_part, float* __restrict__ lse_part) {
+    int sub_shift, int slots_per_wave, int slot_step, float scale_log2, float o_scale, uint16_t* __restrict__ o,
+    float* __restrict__ lse, float* __restrict__ o_part, float* __restrict__ lse_part) {
   __shared__ __align__(16) AttnSmem smw[kAttnWaves];
   __shared__ float mls[kAttnWaves][2][16];
   const int lane = lane_id();
@@ -110,13 +111,16 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void attn_rows_kernel(
   // the wave's slots, one per lane, fetched at once (slots_per_wave <= 64 with
   // ids); without block ids (dense mode) slot b is key block b
   const int nslots = topk << sub_shift;
-  const int slot0 = min(nslots, (sp * kAttnWaves + wv) * slots_per_wave);
-  const int slot1 = min(nslots, slot0 + slots_per_wave);
+  const int first = min(nslots, slot_step > 1 ? sp * kAttnWaves + wv : (sp * kAttnWaves + wv) * slots_per_wave);
+  // the wave's slots are numbered slot0 .. slot1 - 1
+  const int slot0 = first;
+  const int slot1 = slot0 + min(slots_per_wave, (nslots - first + slot_step - 1) / slot_step);
   const int32_t* ids = block_ids ? block_ids + (row * H_kv + r) * topk : nullptr;
   int my_b = -1;
   if (ids && slot0 + lane < slot1) {
-    const int id = ids[(slot0 + lane) >> sub_shift];
-    my_b = id < 0 ? -1 : (id << sub_shift) + ((slot0 + lane) & ((1 << sub_shift) - 1));
+    const int at = first + lane * slot_step;
+    const int id = ids[at >> sub_shift];
+    my_b = id < 0 ? -1 : (id << sub_shift) + (at & ((1 << sub_shift) - 1));
   }
   const int s = find_seq_wave(sq.q_offsets, sq.num_seqs, row);
   const SeqGeom g = seq_geom(sq, s);
@@ -495,6 +499,7 @@ int validate_attn(const msa_seqs* seqs, int H_q, int H_kv, int head_dim, int BK,
 struct SplitPlan {
   int nsplit;           // CTAs per (row, group); above one, partials go through combine_kernel
   int slots_per_wave;
+  int slot_step = 1;    // above one: the waves' slots alternate
 };
 
 // Spread the slots of each (row, group) over kAttnWaves waves per CTA and
@@ -520,6 +525,24 @@ size_t split_workspace(const msa_seqs* seqs, int H_q, const SplitPlan& sp) {
 
 int block_shift(int BK) { return BK == 128 ? 1 : 0; }    // log2 of slots per block
 
+// The split over 64-key slots.  A 128-key block's second slot alone opens no
+// split: up to 4 blocks stay in one CTA, two slots to a wave (k 4, 12 - 184 rows:
+// 12 - 14 us, as two splits and their merge 16 - 18).  Where contexts have fewer
+// blocks than the rows' lists have entries, padding ends every list, and
+// consecutive slots would give the first waves all of the work in a chain of
+// twice as many slots as blocks: the waves' slots alternate (4 groups of 8 heads,
+// 36 rows on 1400 - 4100 keys, k 64: 55 us -> 38; a kernel for whole blocks 43).
+SplitPlan slot_plan(const msa_seqs* seqs, int H_kv, int BK, int topk) {
+  const int shift = block_shift(BK);
+  SplitPlan sp = split_plan(seqs, H_kv, topk << shift);
+  if (shift > 0) {
+    if (sp.nsplit > 1 && split_plan(seqs, H_kv, topk).nsplit == 1)
+      sp = SplitPlan{1, ((topk << shift) + kAttnWaves - 1) / kAttnWaves};
+    if ((seqs->max_kv_len + BK - 1) / BK < topk) sp.slot_step = sp.nsplit * kAttnWaves;
+  }
+  return sp;
+}
+
 // The decode call's split: over 64-key slots, or where the workspace is too
 // small for that many splits over whole blocks.
 int decode_plan(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk, const void* workspace,
@@ -528,11 +551,10 @@ int decode_plan(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk, const
     const size_t need = split_workspace(seqs, H_q, *sp);
     return need == 0 || (workspace && workspace_bytes >= need);
   };
-  const int shift = block_shift(BK);
-  *sp = split_plan(seqs, H_kv, topk << shift);
+  *sp = slot_plan(seqs, H_kv, BK, topk);
   if (fits()) return MSA_OK;
   *sp = split_plan(seqs, H_kv, topk);
-  sp->slots_per_wave <<= shift;
+  sp->slots_per_wave <<= block_shift(BK);
   return fits() ? MSA_OK : MSA_ERR_WORKSPACE;
 }
 
@@ -559,7 +581,7 @@ int run_rows(const void* q, const void* k, const void* v, const int32_t* block_i
     using T = decltype(elem);
     msa_prof::launch("attn_rows_kernel", kernel, grid, block, 0, stream, static_cast<const T*>(q),
                      static_cast<const T*>(k), static_cast<const T*>(v), block_ids, sq, H_q, H_kv, topk,
-                     sub_shift, sp.slots_per_wave, sl2, v_scale, op, lse, o_part, lse_part);
+                     sub_shift, sp.slots_per_wave, sp.slot_step, sl2, v_scale, op, lse, o_part, lse_part);
   };
   if (sq.block_table) {
     if (!fp8) launch(attn_rows_kernel<uint16_t, true>, uint16_t{});
@@ -615,7 +637,7 @@ int msa_rows_dense(const void* q, const void* k, const void* v, const msa_seqs* 
 extern "C" size_t msa_sparse_attn_decode_workspace_size(const msa_seqs* seqs, int num_q_heads, int num_kv_heads,
                                                        int head_dim, int block_size, int topk) {
   if (validate_attn(seqs, num_q_heads, num_kv_heads, head_dim, block_size, topk) != MSA_OK) return 0;
-  return split_workspace(seqs, num_q_heads, split_plan(seqs, num_kv_heads, topk << block_shift(block_size)));
+  return split_workspace(seqs, num_q_heads, slot_plan(seqs, num_kv_heads, block_size, topk));
 }
 
 extern "C" int msa_sparse_attn_decode(const void* q, const void* k, const void* v, const int32_t* block_ids,

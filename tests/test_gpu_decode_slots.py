@@ -31,6 +31,9 @@ CASES = [
     ("one_row_many_splits", [1], [9001], 16, 1, 128, 63, False, False),
     ("one_row_splits_b64", [1], [5001], 64, 4, 64, 63, True, False),
     ("rows_pages", [4, 2, 7], [1500, 66, 7], 48, 16, 128, 8, False, True),
+    # fewer blocks than slots: the waves' slots alternate
+    ("padded_lists", [4, 1, 4], [1451, 2049, 4140], 32, 4, 128, 63, False, False),
+    ("padded_lists_fp8_pages", [2] * 40, [700, 1300] * 20, 64, 16, 128, 15, True, True),
     ("many_rows_one_cta", [8] * 80, [700] * 80, 32, 8, 128, 4, True, False),
 ]
 
@@ -83,3 +86,14 @@ def test_decode_slots(case):
     fin = torch.isfinite(lse)
     assert torch.equal(fin, torch.isfinite(lw)) and float((lse - lw)[fin].abs().max()) <= 1e-5
     assert float((o.double() - ow.double()).norm() / ow.double().norm()) <= 5e-3
+
+
+@pytest.mark.parametrize("topk,splits", [(3, 1), (4, 1), (5, 3)])
+def test_few_blocks_take_one_cta(topk, splits):
+    """Up to four 128-key blocks are one CTA's eight slots; from five on (two
+    CTAs as whole blocks) every four slots are a split."""
+    p = synth.packed_problem(f"one_cta_{topk}", [1], [3000], num_q_heads=64, num_kv_heads=4, block_size=128, topk=topk,
+                             seed=topk)
+    seqs = msa.Seqs.from_problem(p, torch.device("cuda"))
+    need = 0 if splits == 1 else splits * 64 * 128 * 4 + splits * 64 * 4
+    assert msa.lib().msa_sparse_attn_decode_workspace_size(seqs.ref(), 64, 4, 128, 128, topk) == need
