@@ -42,7 +42,9 @@ constexpr double kTileReach = BK == 64 ? 4.0 : 2.5;
 constexpr int64_t kMinTileCtas = 128;
 // With rows left for the key-block-outer kernels as well, the tiles have to
 // fill the chip (two CTAs per CU: below that they add their own latency, 49 us
-// for 2048 rows of 8 heads, to what the others take anyway), and the longest
+// for 2048 rows of 8 heads, to what the others take anyway; counted without the
+// grid's CTAs of rows past the cut: 3 sequences of up to 4245 rows, 16 heads on 1
+// group, k 4, 189 us key-block-outer and 199 with tiles), and the longest
 // sequence has to start low (700-row chunks on contexts of 3000 - 6000, k 16:
 // 519 us without tiles, 544 with tiles below position 4096).
 constexpr int64_t kMinSplitCtas = 512;
@@ -111,7 +113,14 @@ int msa_tile_positions(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk
   flash::plan_grid(seqs, qt, cut, &tiles);
   const int64_t ctas = tiles * H_kv;
   if (ctas < kMinTileCtas || ctas >= (int64_t(1) << 31)) return 0;
-  if (cut < len && (ctas < kMinSplitCtas || 2 * context > reach)) return 0;
+  if (cut < len) {
+    // tiles that can hold a row below the cut: those of a longest sequence, and
+    // of the others with the remaining rows
+    const int64_t per_seq = (std::min<int64_t>(seqs->max_q_rows, cut) + qt - 1) / qt;
+    const int64_t others = std::min((seqs->num_seqs - 1) * per_seq,
+                                    std::max<int64_t>(rows - seqs->max_q_rows, 0) / qt + seqs->num_seqs - 1);
+    if ((per_seq + others) * H_kv < kMinSplitCtas || 2 * context > reach) return 0;
+  }
   return static_cast<int>(cut);
 }
 

@@ -140,6 +140,28 @@ def test_chunk_of_few_tiles(keys, kernel):
     assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
 
 
+@pytest.mark.parametrize("rows,tiles", [([4245, 1500, 1517], False), ([4245, 1500, 1517, 1100], True)])
+def test_split_counts_tiles_below_the_cut(rows, tiles):
+    """16 heads on one group, k 4: rows below position 1024 are 128 tiles a
+    sequence; a split needs 512 of them, whatever rows lie past."""
+    p = synth.packed_problem(f"split_{len(rows)}", rows, rows, num_q_heads=16, num_kv_heads=1, topk=4, seed=7)
+    x = synth.generate_numpy(p)
+    q, k, v, seqs = *(to_dev(x[n]) for n in "qkv"), msa.Seqs.from_problem(p, torch.device("cuda"))
+    ids = torch.from_numpy(synth.random_block_ids(p)).cuda()
+    msa.profile_reset()
+    msa.profile_enable(True)
+    try:
+        o, lse = msa.sparse_attn_prefill(q, k, v, ids, seqs, 64)
+        torch.cuda.synchronize()
+    finally:
+        msa.profile_enable(False)
+    assert ("tile_attn_kernel" in msa.profile_read()) == tiles
+    msa.profile_reset()
+    od, ld = msa.sparse_attn_decode(q, k, v, ids, seqs, 64)
+    assert float((lse - ld).abs().max()) <= 1e-4
+    assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
+
+
 @pytest.mark.parametrize("blocks", [1, 1365, 1366, 5461, 5462])
 def test_reverse_index_scan_sizes(blocks):
     """Three groups: 3, 4095 and 4098 tiles around one quad of counts a thread,
