@@ -1360,31 +1360,31 @@ constexpr int kNarrowDepth = D == 64 ? 4 : 2;
 // Narrow kernel: a wave scores a slice of 8 blocks, four to a CTA, or a piece of
 // 4 in a CTA of its own.  Pieces halve the wave's chain of rounds, which is the
 // time of small calls, and spread evenly over the CUs; slices stream the same
-// with less setup.  With 64-wide indexes pieces win or tie up to five rounds of
-// slice CTAs.  With 128-wide ones, whose waves hold half as many per CU, only
-// where the slice CTAs would fill less than half of the CUs or one whole round,
-// or leave a last round that fills less than half.  Scores and Top-k, slices
-// against pieces in us, keys read from memory (from the last-level cache):
-//   d_idx 128, 128-key blocks, rows x keys [slice CTAs]:  1 x 13K [4] 31 / 15
-//   (21 / 11), 8 x 51K [104] 38.9 / 36.7 (24.5 / 24.5), 40 x 13K [160] 44.6 / 47.3
-//   (27.9 / 31.9), 16 x 51K [208] 61.5 / 63.0 (40.3 / 41.1), 64 x 13K [256] 64.3 /
-//   60.3 (45.2 / 40.6), 17 x 65K [272] 90.9 / 82.8, 8 x 192K [376] 103.6 / 99.4
-//   (82.5 / 78.6), 32 x 51K [416] 106.1 / 106.4 (79.9 / 83.7), 128 x 13K [512]
-//   107.0 / 107.2 (79.4 / 84.7), 40 x 51K [520] 142.9 / 128.9 (110 / 101), 64 x 51K
-//   [832] 192 / 183 (161 / 152), 32 x 192K [1504] 301 / 303 (266 / 273);
+// with less setup.  Lengths decide as much as sizes: where they differ, slices
+// leave most CUs idle, and the host does not know them.  Scores and Top-k, slices
+// against pieces in us, keys read from memory (from the last-level cache), rows x
+// keys [slice CTAs], lengths from an eighth of that to that (..) or equal:
+//   d_idx 128, 128-key blocks:  1 x 8K [2] 29.4 / 14.5 (21.2 / 11.4), 25 x ..12K
+//   [75] 37.2 / 23.4 (23.0 / 13.2), 44 x ..11K [132] 39.5 / 31.4 (23.3 / 17.4), 62 x
+//   ..26K [434] 98.6 / 84.1 (44.8 / 36.9), 64 x ..100K [1600] 189 / 167 (134 / 112);
+//   40 x 13K [160] 60.3 / 62.8 (26.8 / 30.9), 17 x 33K [153] 66.2 / 67.0 (28.8 /
+//   32.3), 16 x 51K [208] 86.9 / 86.2 (37.7 / 38.1), 32 x 51K [416] 135 / 137 (78.5 /
+//   81.7), 64 x 51K [832] 214 / 206 (157 / 151), 32 x 192K [1504] 330 / 320 (271 / 268);
+//   d_idx 128, 64-key blocks:  8 x ..35K [144] 26.7 / 23.1 (16.2 / 13.2), 50 x ..35K
+//   [900] 103.5 / 96.1 (44.5 / 42.1), 64 x 13K [448] 90.3 / 91.5 (38.1 / 40.4), 40 x
+//   51K [1000] 153 / 157 (97.3 / 102.8), 64 x 51K [1600] 213 / 217 (154 / 162);
 //   d_idx 64, 64-key blocks:  1 x 6K [4] 14.6 / 11.1 (11.1 / 8.3), 40 x 6K [160] 20.9
 //   / 21.2 (15.8 / 14.0), 17 x 33K [272] 30.8 / 28.1, 32 x 26K [416] 35.4 / 37.0 (26.1 /
 //   27.0), 128 x 6K [512] 36.2 / 37.2 (28.0 / 26.1), 200 x 6K [800] 51.2 / 48.9 (40.0 /
-//   34.3), 64 x 26K [832] 61.7 / 60.3 (41.5 / 40.4), 32 x 96K [1504] 95.0 / 97.7 (78.4 / 80.2).
+//   34.3), 64 x 26K [832] 61.7 / 60.3 (41.5 / 40.4), 32 x 96K [1504] 95.0 / 97.7 (78.4 /
+//   80.2), 47 x ..64K [1504] (37.2 / 33.7).
+// So pieces up to the rounds of slices from which they lose at equal lengths; the
+// most they cost below is 15 % at equal lengths held in the last-level cache.
 constexpr int64_t kCus = 256;
+constexpr int64_t kNarrowPieceMaxSlices = 3 * 2048;
 constexpr int kNarrowPieceBlocks = 4;
-bool narrow_pieces(const IndexPlan& pl, int d_idx, int64_t units) {
-  const int64_t slices = (pl.bcap + kSliceBlocks - 1) / kSliceBlocks;
-  const int64_t ctas = units * ((slices + kWaves - 1) / kWaves);
-  if (!pl.narrow) return false;
-  if (d_idx == 64) return ctas < 5 * kCus;
-  const bool one_round = ctas > kCus - kCus / 8 && ctas <= kCus;
-  return ctas < 5 * kCus && ((ctas - 1) % kCus < kCus / 2 || one_round);
+bool narrow_pieces(const IndexPlan& pl, int64_t units) {
+  return pl.narrow && units * ((pl.bcap + kSliceBlocks - 1) / kSliceBlocks) < kNarrowPieceMaxSlices;
 }
 
 // Wave kernel: a CTA's operand loads take what its CU's address unit gives, so
@@ -1417,7 +1417,7 @@ void launch_scores_as(const IndexPlan& pl, dim3 grid, hipStream_t stream, const 
     msa_prof::launch("index_block_max_lds_kernel", (index_block_max_lds_kernel<D, B, 64, PAGED>), grid, dim3(256), 0,
                      stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, cta_blocks, M, static_cast<int64_t>(pl.bcap), CM,
                      cm_stride, PM);
-  else if (narrow_pieces(pl, D, u1 - u0))
+  else if (narrow_pieces(pl, u1 - u0))
     msa_prof::launch("index_block_max_narrow_kernel",
                      (index_block_max_narrow_kernel<D, B, kNarrowDepth<D, B>, kNarrowPieceBlocks, 1, PAGED>), grid,
                      dim3(kWave), 0, stream, iq, ik, sq, unit_shift, H_kv, pl.qr, u0, u1, M,
@@ -1486,7 +1486,7 @@ int index_topk_run(const IndexPlan& pl, const void* index_q, const void* index_k
     const unsigned ny = static_cast<unsigned>((pl.bcap + cta_blocks - 1) / cta_blocks);
     float* cm = cta_blocks == kBlocksPerCta ? CM : nullptr;
     // per-wave kernels: slices (or pieces) of consecutive blocks, one per wave
-    const bool pieces = narrow_pieces(pl, d_idx, u1 - u0);
+    const bool pieces = narrow_pieces(pl, u1 - u0);
     const int wave_blocks = pieces ? kNarrowPieceBlocks : kSliceBlocks;
     const int cta_waves = pieces ? 1 : kWaves;
     const int nslice = (pl.bcap + wave_blocks - 1) / wave_blocks;
