@@ -532,13 +532,16 @@ int block_shift(int BK) { return BK == 128 ? 1 : 0; }    // log2 of slots per bl
 // consecutive slots would give the first waves all of the work in a chain of
 // twice as many slots as blocks: the waves' slots alternate (4 groups of 8 heads,
 // 36 rows on 1400 - 4100 keys, k 64: 55 us -> 38; a kernel for whole blocks 43).
+// Chains of a few slots are no longer for it, and fewer waves then start at all (51
+// rows on 264 - 1853 keys, k 16, 4 slots a wave: 31 us, alternating 34).
+constexpr int kStepSlots = 6;
 SplitPlan slot_plan(const msa_seqs* seqs, int H_kv, int BK, int topk) {
   const int shift = block_shift(BK);
   SplitPlan sp = split_plan(seqs, H_kv, topk << shift);
   if (shift > 0) {
     if (sp.nsplit > 1 && split_plan(seqs, H_kv, topk).nsplit == 1)
       sp = SplitPlan{1, ((topk << shift) + kAttnWaves - 1) / kAttnWaves};
-    if ((seqs->max_kv_len + BK - 1) / BK < topk) sp.slot_step = sp.nsplit * kAttnWaves;
+    if ((seqs->max_kv_len + BK - 1) / BK < topk && sp.slots_per_wave >= kStepSlots) sp.slot_step = sp.nsplit * kAttnWaves;
   }
   return sp;
 }

@@ -31,9 +31,10 @@ CASES = [
     ("one_row_many_splits", [1], [9001], 16, 1, 128, 63, False, False),
     ("one_row_splits_b64", [1], [5001], 64, 4, 64, 63, True, False),
     ("rows_pages", [4, 2, 7], [1500, 66, 7], 48, 16, 128, 8, False, True),
-    # fewer blocks than slots: the waves' slots alternate
-    ("padded_lists", [4, 1, 4], [1451, 2049, 4140], 32, 4, 128, 63, False, False),
+    # fewer blocks than slots: the waves' slots alternate from six a wave on
+    ("padded_lists", [4, 1, 4] * 12, [1451, 2049, 4140] * 12, 32, 4, 128, 63, False, False),
     ("padded_lists_fp8_pages", [2] * 40, [700, 1300] * 20, 64, 16, 128, 15, True, True),
+    ("padded_lists_few_slots", [4, 1, 4], [1451, 2049, 4140], 32, 4, 128, 63, False, False),
     ("many_rows_one_cta", [8] * 80, [700] * 80, 32, 8, 128, 4, True, False),
 ]
 
