@@ -47,7 +47,13 @@ constexpr int64_t kMinTileCtas = 128;
 // group, k 4, 189 us key-block-outer and 199 with tiles), and the longest
 // sequence has to start low (700-row chunks on contexts of 3000 - 6000, k 16:
 // 519 us without tiles, 544 with tiles below position 4096).
-constexpr int64_t kMinSplitCtas = 512;
+// Tiles of few keys are over sooner, and groups of one head save more (below):
+// they need fewer CTAs (4316 rows in 6 sequences, 32 heads on 16 groups, k 1 of
+// 128-key blocks, 480 tiles of up to 320 keys: 136 us and 148 without; 17157 in 9, 12
+// on 2, 288 tiles: 148 and 162; 21736 in 2, 48 on 16, 256 tiles: 731 and 718; 12534
+// in 3, 8 heads on 8 groups, k 16, 456 tiles: 430 and 515).
+constexpr int64_t kMinSplitCtas = 512, kMinFewSplitCtas = 256;
+constexpr int64_t kShortChain = 512;
 // A call of prompts whose last positions lie past the reach stays in tiles
 // altogether when that costs less than the launches of the other path (about
 // 75 us): the scores past the reach, and what the longest tile (1.5 us per 64
@@ -70,7 +76,13 @@ constexpr int64_t kMinMeanRows = 256;                 // ... for prompts: short 
 // 150.  (Of 2148 chunk calls of 256 rows and more per sequence, sequences of
 // equal and of mixed lengths, 12 remain 3 - 14 % slower in tiles than they were
 // key-block-outer only, most where 576 - 760 tiles make a thin second round.)
+// Groups of one head cost key-block-outer rows as much as groups of two: 2276
+// rows of 8 heads on 8 groups, 128-key blocks, k 48, up to 9506 keys 207 us in
+// tiles and 350; 5999 rows of 4 on 4, 64-key blocks, k 64, 14138 keys 308 and 378.
+// 128-key blocks take the upper end of their reach, 3.3 (1150 rows of 24 on 8, k 48,
+// 12460 keys: 267 and 310).
 constexpr int64_t kTileSlots = 512;
+constexpr int kMinGroupHeads = 2;
 
 template <typename T, int BK, bool PAGED>
 int launch_tiles(const void* q, const void* k, const void* v, const int32_t* block_ids, const msa_seqs* seqs,
@@ -107,7 +119,9 @@ int msa_tile_positions(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk
     const int64_t per_seq = (seqs->max_q_rows + qt - 1) / qt;
     const bool one_round =
         std::min(rows / qt + seqs->num_seqs, seqs->num_seqs * per_seq) * H_kv <= kTileSlots;
-    if (context > 0 && cut >= len && one_round && kTileUsPerKey * len > kOuterLaunchUs + per_score * rows * reach) return 0;
+    const double row_keys = (BK == 64 ? 4.0 : 3.3) * topk * BK;   // the upper end of the reach
+    const double outer = kTileUsPerScore * H_kv * std::max(H_q / H_kv, kMinGroupHeads) * rows * row_keys;
+    if (context > 0 && cut >= len && one_round && kTileUsPerKey * len > kOuterLaunchUs + outer) return 0;
   }
   int64_t tiles;
   flash::plan_grid(seqs, qt, cut, &tiles);
@@ -119,7 +133,8 @@ int msa_tile_positions(const msa_seqs* seqs, int H_q, int H_kv, int BK, int topk
     const int64_t per_seq = (std::min<int64_t>(seqs->max_q_rows, cut) + qt - 1) / qt;
     const int64_t others = std::min((seqs->num_seqs - 1) * per_seq,
                                     std::max<int64_t>(rows - seqs->max_q_rows, 0) / qt + seqs->num_seqs - 1);
-    if ((per_seq + others) * H_kv < kMinSplitCtas || 2 * context > reach) return 0;
+    const bool few = cut <= kShortChain || H_q / H_kv < kMinGroupHeads;
+    if ((per_seq + others) * H_kv < (few ? kMinFewSplitCtas : kMinSplitCtas) || 2 * context > reach) return 0;
   }
   return static_cast<int>(cut);
 }

@@ -140,24 +140,30 @@ def test_chunk_of_few_tiles(keys, kernel):
     assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
 
 
-@pytest.mark.parametrize("rows,tiles", [([4245, 1500, 1517], False), ([4245, 1500, 1517, 1100], True)])
-def test_split_counts_tiles_below_the_cut(rows, tiles):
-    """16 heads on one group, k 4: rows below position 1024 are 128 tiles a
-    sequence; a split needs 512 of them, whatever rows lie past."""
-    p = synth.packed_problem(f"split_{len(rows)}", rows, rows, num_q_heads=16, num_kv_heads=1, topk=4, seed=7)
+@pytest.mark.parametrize("rows,H_q,H_kv,bk,tiles", [
+    ([4245, 1500, 1517], 16, 1, 64, False),               # 128 tiles a sequence, 512 needed
+    ([4245, 1500, 1517, 1100], 16, 1, 64, True),
+    ([6000, 1500, 1517], 8, 8, 128, False),               # heads alone: 10 tiles a group and sequence, 256 needed
+    ([6000, 1500, 1517, 1300, 1300], 8, 8, 128, True),
+])
+def test_split_counts_tiles_below_the_cut(rows, H_q, H_kv, bk, tiles):
+    """k 4: a split needs its number of tiles below position 1024 (1280 of
+    128-key blocks), whatever rows lie past."""
+    p = synth.packed_problem(f"split_{len(rows)}_{H_kv}", rows, rows, num_q_heads=H_q, num_kv_heads=H_kv, block_size=bk,
+                             topk=4, seed=7)
     x = synth.generate_numpy(p)
     q, k, v, seqs = *(to_dev(x[n]) for n in "qkv"), msa.Seqs.from_problem(p, torch.device("cuda"))
     ids = torch.from_numpy(synth.random_block_ids(p)).cuda()
     msa.profile_reset()
     msa.profile_enable(True)
     try:
-        o, lse = msa.sparse_attn_prefill(q, k, v, ids, seqs, 64)
+        o, lse = msa.sparse_attn_prefill(q, k, v, ids, seqs, bk)
         torch.cuda.synchronize()
     finally:
         msa.profile_enable(False)
     assert ("tile_attn_kernel" in msa.profile_read()) == tiles
     msa.profile_reset()
-    od, ld = msa.sparse_attn_decode(q, k, v, ids, seqs, 64)
+    od, ld = msa.sparse_attn_decode(q, k, v, ids, seqs, bk)
     assert float((lse - ld).abs().max()) <= 1e-4
     assert float((o.double() - od.double()).norm() / od.double().norm()) <= 5e-3
 
